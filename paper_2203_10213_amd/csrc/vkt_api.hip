@@ -543,7 +543,8 @@ bool mfma_row_pairs(const FilterJob& j, bool six_products)
     const int64_t cells =
         (int64_t)(j.roi[3] - j.roi[0]) * (j.roi[4] - j.roi[1]) * (j.roi[5] - j.roi[2]);
     return (j.k == 5 || (j.k == 7 && j.fmt == vktDataFormatFloat32 && !six_products)) &&
-           cells > state().row_pair_min_cells;
+           cells > state().row_pair_min_cells &&
+           (int64_t)j.X * j.Y >= 4;  // (its staging loads 4-cell windows of a plane)
 }
 
 hipError_t launch_filter_mfma(const FilterJob& j, bool six_products, hipStream_t s)

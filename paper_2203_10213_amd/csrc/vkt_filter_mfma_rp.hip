@@ -8,76 +8,84 @@
 //
 // GEMM embedding, per input plane zi (D += A * B on 32x32x16 tiles):
 //   N (columns n) : row pairs of one x-strip: output rows y0 + 2n + dy,
-//                   dy in {0, 1}, of NX = 2 output columns;
+//                   dy in {0, 1}, of NX output columns (3 for k = 5, 2 for 7);
 //   K (reduction) : (row offset b' in 0..k, input column ax in 0..7) pairs,
 //                   two rows per 16-deep chunk; the B operand is the input
 //                   window s(x_s - r + ax, y0 + 2n + b' - r, zi), read
 //                   straight from the LDS-staged plane;
 //   M (rows)      : (filter plane c, dy, output x-offset xo), with
 //                   A[(c, dy, xo)][(b', ax)] = w[c][b' - dy][ax - xo]
-//                   (zero outside the filter), kept in registers.
+//                   (zero outside the filter).
 // Pairing output rows lets one 16-deep chunk carry two filter rows for both
-// rows of a pair: for k = 7 the 49 taps of a (c, dy, xo) row fill 49 of 64
-// reduction slots and 28 of the 32 M rows are used (67 % of the products are
-// filter taps), and each MFMA does twice the work of a 16x16x32 one for the
-// same 1 KB input operand, which halves the LDS reads per output.
+// rows of a pair.  k = 7: 28 of the 32 M rows and 49 of 64 reduction slots are
+// filter taps (67 % of the products); k = 5 with three columns a strip: 30 of
+// 32 and 25 of 48 (49 %; with two columns 33 %, and half as many products
+// again for the same outputs).  The sum of one row's 8 slots does not depend
+// on their order (checked on the GPU with permuted slots), so a strip's width
+// changes no result.
 //
 // z ring in registers: lane l holds D rows 8 (r / 4) + 4 (l / 32) + r % 4
-// in its registers r = 0..15.  M row (c, dy, xo) is placed at register
-// r = 2 c + dy of lane half xo, so register r of either half accumulates the
-// contribution of input plane zi to output plane zi - c + r_f (r_f = filter
-// radius).  After each input plane registers 2k-2, 2k-1 hold a finished
-// output plane (c = k - 1), and the ring advances by register renaming:
-// r <- r - 2 (registers 0 and 1 restart at zero) -- no lane crosses.
+// in its registers r = 0..15.  M row (c, dy, xo) is placed in lane half dy at
+// register NX s + xo of ring slot s; slot s accumulates output plane s mod k
+// of the slab, so the filter plane that it meets moves on with each input
+// plane, not the accumulators: a lane reads its 16-byte weight row of the next
+// filter plane from a table in LDS (8 reads of 1 KB a plane and wave for k = 7
+// instead of some 110 register moves; vector instructions without the products
+// 327 -> 143 a plane and wave).  Lane l then holds output row
+// y0 + 2 (l % 32) + l / 32 of its wave's strips.
 //
-// Output: for each strip, the finished registers of the two lane halves are
-// exchanged with v_permlane32_swap, after which lane l holds output row
-// y0 + 2 (l % 32) + l / 32 at the strip's two columns; a wave's four strips
-// give each lane 8 consecutive cells of one row, rounded and stored with one
-// vector store (no LDS transposition).
+// A workgroup is 4 waves x 4 strips: a tile of 48 (k = 5) or 32 (k = 7)
+// columns and 64 rows; a wave's 4 strips are adjacent, and one segment read
+// per (K chunk, operand piece) holds all their windows.
 //
-// A workgroup is 4 waves x 4 strips x 2 columns = a 32-wide, 64-tall tile;
-// a wave's 4 strips are adjacent, so two 16-byte LDS reads per (K chunk,
-// operand piece) hold all four strips' 16-byte windows (dword offsets 0..3),
-// and the products issue products-outer/strips-inner (four independent
-// accumulators between dependent MFMAs).
+// What bounds it: the matrix cores (busy 77 % at 7^3, 57 % at 5^3 with 6
+// products, 37 % for uint8) at the clock that the card holds under them (1.5
+// to 1.7 GHz for float32).  Measured before and after the face quads of their
+// own, the strips of three columns, the turning weights and the rising
+// priorities: 302^3 uint8 5^3 106 -> 46 us, 512^3 float32 5^3 with 6 products
+// 455 -> 409 us, 1024^3 7^3 with 3 products 2.97 -> 2.75 ms, all with the same
+// bits as before.
 #include "vkt_mfma_common.h"
 
 #include <type_traits>
+#include <utility>
 
 namespace vkt {
 namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-// Pieces of two adjacent cells, packed as the dword pairs they are staged
-// as (cell 0 in the low half): the same splitting as split_voxel, with the
-// float32 pieces converted two at a time.
+// Pieces of two adjacent cells, packed as the dword pairs they are staged as
+// (cell 0 in the low half): the pieces of split_voxel, converted two at a
+// time (one v_cvt_pk per pair; cells and their uint16 halves are exact in
+// fp16, so that the round-toward-zero packing changes nothing).
 template <int PM, typename T>
 __device__ inline void split_pair(T s0, T s1, uint32_t* pk)
 {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     if constexpr (PM == kF32x3 || PM == kF32x6) {
         const float x0 = (float)s0, x1 = (float)s1;
-        const uint32_t hu = (uint32_t)bf16_bits(x0) | ((uint32_t)bf16_bits(x1) << 16);
+        const uint32_t hu =
+            __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{x0, x1}), bf16x2));
         const float r0 = x0 - __uint_as_float(hu << 16), r1 = x1 - __uint_as_float(hu & 0xffff0000u);
-        const uint32_t lu = (uint32_t)bf16_bits(r0) | ((uint32_t)bf16_bits(r1) << 16);
+        const uint32_t lu =
+            __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{r0, r1}), bf16x2));
         pk[0] = hu;
         pk[1] = lu;
         if constexpr (PM == kF32x6) {
             const float t0 = r0 - __uint_as_float(lu << 16), t1 = r1 - __uint_as_float(lu & 0xffff0000u);
-            pk[2] = (uint32_t)bf16_bits(t0) | ((uint32_t)bf16_bits(t1) << 16);
+            pk[2] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{t0, t1}), bf16x2));
         }
+    } else if constexpr (PM == kU16) {
+        const uint32_t v0 = s0, v1 = s1;
+        pk[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz((float)(v0 & 0xff00u),
+                                                                        (float)(v1 & 0xff00u)));
+        pk[1] = __builtin_bit_cast(uint32_t,
+                                   __builtin_amdgcn_cvt_pkrtz((float)(v0 & 255u), (float)(v1 & 255u)));
     } else {
-        uint16_t p0[3], p1[3];
-        split_voxel<PM>(s0, p0);
-        split_voxel<PM>(s1, p1);
-#pragma unroll
-        for (int ps = 0; ps < Pieces<PM>::PS; ++ps) pk[ps] = (uint32_t)p0[ps] | ((uint32_t)p1[ps] << 16);
+        pk[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz((float)s0, (float)s1));
     }
 }
-
-// Output transposition rows: 32 floats + 4 of padding (rows two apart fall
-// in different banks)
-constexpr int kEpiPitch = 36;
 
 template <typename T, int K, int PM>
 struct RpCfg {
@@ -85,20 +93,38 @@ struct RpCfg {
     using PC = Pieces<PM>;
     static constexpr int R = (K - 1) / 2;
     static_assert(K == 5 || K == 7, "filters of 5 or 7");
-    static constexpr int NX = 2;                    // output columns per strip
+    static constexpr int NX = K == 5 ? 3 : 2;       // output columns per strip
+    static_assert(NX + K - 1 <= 8 && K * NX <= 16, "8 input columns, 16 registers");
     static constexpr int WS = 4;                    // strips per wave
+    static constexpr int WX = WS * NX;              // columns per wave
     static constexpr int NCH = (K + 2) / 2;         // 16-deep chunks: rows b' = 0..k
-    static constexpr int TX = 4 * WS * NX;          // 32 columns per workgroup
+    static constexpr int TX = 4 * WX;               // columns per workgroup
     static constexpr int TY = 64;                   // 32 row pairs
     static constexpr int HY = TY + K - 1;           // staged rows
-    static constexpr int PITCH = 40;                // staged columns (x0 - r ...)
-    static_assert(TX + K - 1 <= PITCH && 8 * 3 + 16 <= PITCH, "staged columns");
+    static constexpr int PITCH = K == 5 ? 56 : 40;  // staged columns (x0 - r ...)
+    // staged rows lie in pairs of PAIR cells: the lanes of a segment read are
+    // one pair apart, and 58 dwords put the 8-byte reads of 16 lanes into
+    // different banks (56: 74 cycles for 40 bytes a lane instead of 24)
+    static constexpr int PAIR = K == 5 ? 116 : 80;
+    static constexpr int at(int row, int col) { return (row >> 1) * PAIR + (row & 1) * PITCH + col; }
+    // dwords of a lane's segment: the windows of the wave's strips, read 8
+    // bytes (24-byte wave offsets, k = 5) or 16 bytes at a time
+    static constexpr int RD = WX % 8 == 0 ? 4 : 2;
+    static constexpr int SEGD = ((NX * (WS - 1) + 8 + 1) / 2 + RD - 1) / RD * RD;
+    static_assert(TX + K - 1 <= PITCH && 3 * WX + 2 * SEGD <= PITCH && PITCH % 8 == 0, "columns");
     static_assert(2 * 31 + 2 * (NCH - 1) + 1 < HY, "staged rows");
-    static constexpr int PLANE = HY * PITCH;
-    static constexpr int RFIN = 2 * K - 2;          // finished registers RFIN, RFIN + 1
-    // planes whose cells are in flight in registers: two (loads issued two
-    // planes ahead) except for 6-product float32, which is short of registers
-    static constexpr int PF = PM == kF32x6 ? 1 : 2;
+    static constexpr int PLANE = (HY / 2 * PAIR + 7) / 8 * 8;
+    static_assert(HY % 2 == 0, "row pairs");
+    static constexpr int NQ = HY * PITCH / 4;       // staged quads
+    // output rows in LDS (floats), read and written EV floats at a time
+    static constexpr int EV = K == 5 ? 2 : 4;
+    static constexpr int EPITCH = TX + EV;
+    // weight table in LDS: per (chunk, piece, lane half) the 16-byte rows of
+    // (c, dy, xo), then a zero row for the unused M rows
+    static constexpr int AROWS = 2 * NX * K + 1;
+    static constexpr int TABLE = NCH * PC::NBI * 2 * AROWS * 8;  // 16-bit elements
+    static constexpr int LDS_BYTES = (2 * PC::PS * PLANE + TABLE) * 2 + 2 * TY * EPITCH * 4;
+    static_assert(2 * LDS_BYTES <= 160 * 1024, "two workgroups per CU");
 };
 
 // Four consecutive cells at byte offset off (4-byte aligned): one 4-, 8- or
@@ -124,6 +150,18 @@ __device__ inline void buf_load4(__amdgpu_buffer_rsrc_t r, uint32_t off, T (&v)[
     }
 }
 
+template <typename F, int... I>
+__device__ __attribute__((always_inline)) inline void static_for_impl(
+    F& f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __attribute__((always_inline)) inline void static_for(F&& f)
+{
+    static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+
 template <bool F16>
 __device__ inline f32x16 mfma32(u16x8 a, u32x4 b, f32x16 c)
 {
@@ -137,7 +175,7 @@ __device__ inline f32x16 mfma32(u16x8 a, u32x4 b, f32x16 c)
 
 template <class C>
 __device__ void rp_tile(const VolDesc& a, const float* __restrict__ w, int tile, int slab,
-                        uint16_t* lds_base, float (*epi)[64][kEpiPitch])
+                        uint16_t* lds_base, float (*epi)[C::TY][C::EPITCH], uint16_t* tab)
 {
     using T = typename C::Tin;
     using PC = typename C::PC;
@@ -147,7 +185,7 @@ __device__ void rp_tile(const VolDesc& a, const float* __restrict__ w, int tile,
                        : std::is_same<T, uint16_t>::value ? kU16
                        : (PC::NPROD == 6 ? kF32x6 : kF32x3);
     constexpr int PLANE = C::PLANE;
-    // lds[buffer][piece][row * PITCH + column]
+    // lds[buffer][piece][C::at(row, column)]
     auto lds = reinterpret_cast<uint16_t(*)[PC::PS][PLANE]>(lds_base);
 
     const int t = threadIdx.x, lane = t % 64, wave = t / 64;
@@ -156,110 +194,161 @@ __device__ void rp_tile(const VolDesc& a, const float* __restrict__ w, int tile,
     const int64_t plane = (int64_t)a.X * a.Y;
     const int32_t plane_bytes = (int32_t)(plane * (int64_t)sizeof(T));  // < 2^31 (host check)
 
-    // ---- A operand (weights): lane l holds M row l % 32 = (c, dy, xo) and
-    // the 8 reduction slots (b' = 2q + l / 32, ax = 0..7) of chunk q
-    u16x8 W[C::NCH][PC::NBI];
+    // ---- A operand (weights): row (c, dy, xo) of the table holds, per chunk
+    // q, piece and lane half kg, the 8 reduction slots (b' = 2q + kg,
+    // ax = 0..7); a thread builds one (q, kg, row)
+    for (int i = t; i < C::NCH * 2 * C::AROWS; i += kNT) {
+        const int row = i % C::AROWS, kg = (i / C::AROWS) % 2, q = i / (2 * C::AROWS);
+        const int c = row / (2 * C::NX), dy = (row / C::NX) % 2, xo = row % C::NX;
+        u16x8 v[PC::NBI];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int b = 2 * q + kg - dy, aa = e - xo;
+            float wv = 0.f;
+            if (c < K && b >= 0 && b < K && aa >= 0 && aa < K) wv = w[(c * K + b) * K + aa];
+            uint16_t p[3];
+            split_weight<PM>(wv, a.wscale, p);
+#pragma unroll
+            for (int bi = 0; bi < PC::NBI; ++bi) v[bi][e] = p[bi];
+        }
+#pragma unroll
+        for (int bi = 0; bi < PC::NBI; ++bi)
+            *reinterpret_cast<u16x8*>(&tab[(((q * PC::NBI + bi) * 2 + kg) * C::AROWS + row) * 8]) = v[bi];
+    }
+    // Lane l's M row is register r of lane half dy: ring slot r / NX, column
+    // xo.  Slot s holds output plane s mod k of the slab, so at input plane p
+    // it takes filter plane c = (p - s) mod k: the lane reads the table one
+    // filter plane (ASTEP elements) further each plane.
+    constexpr int ASTEP = 2 * C::NX * 8;
+    int aoff, alast, afirst;
     {
         const int rho = lane % 32, kg = lane / 32;
-        const int r = 4 * (rho / 8) + rho % 4, xo = (rho / 4) % 2;
-        const int c = r / 2, dy = r % 2;
-#pragma unroll
-        for (int q = 0; q < C::NCH; ++q) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int b = 2 * q + kg - dy, aa = e - xo;
-                float wv = 0.f;
-                if (c < K && b >= 0 && b < K && aa >= 0 && aa < K) wv = w[(c * K + b) * K + aa];
-                uint16_t p[3];
-                split_weight<PM>(wv, a.wscale, p);
-#pragma unroll
-                for (int bi = 0; bi < PC::NBI; ++bi) W[q][bi][e] = p[bi];
-            }
-        }
-        // pin the pieces in registers: without this the compiler keeps the
-        // float weights and splits them again for every plane
-#pragma unroll
-        for (int q = 0; q < C::NCH; ++q)
-#pragma unroll
-            for (int bi = 0; bi < PC::NBI; ++bi) {
-                u32x4 v = __builtin_bit_cast(u32x4, W[q][bi]);
-                asm volatile("" : "+v"(v));
-                W[q][bi] = __builtin_bit_cast(u16x8, v);
-            }
+        const int r = 4 * (rho / 8) + rho % 4, dy = (rho / 4) % 2;
+        const int sl = r / C::NX, xo = r % C::NX;
+        afirst = (kg * C::AROWS + (sl < K ? dy * C::NX + xo : C::AROWS - 1)) * 8;
+        alast = afirst + (sl < K ? (K - 1) * ASTEP : 0);
+        aoff = afirst + (sl < K ? (K - sl) % K * ASTEP : 0);
     }
 
     // ---- staging of the input plane: PITCH x HY cells from (x0 - r, y0 - r),
-    // four adjacent cells (a quad) per thread and step: one 4-cell load when
-    // the quad lies inside its source row, else four cell loads through the
-    // address mode (quads at the volume's x faces)
-    constexpr int NQ = C::PLANE / 4;
+    // four adjacent cells (a quad) per thread and step, one 4-cell load each
+    // and no branch around it.  Quads that reach past an x face of the volume
+    // (at most three a row: one with columns left of cell 0, two with columns
+    // from X to X + r - 1) are staged apart, one per thread, by four cell
+    // loads through the address mode; only tiles at a face have any (a
+    // wave-uniform branch), and a quad past X + r stays zero, as it meets
+    // zero weights.  With the loads of a step fixed in number the compiler
+    // waits for exactly the plane it stages: four cell loads in a divergent
+    // branch for the face quads, as this kernel had them, put a memory latency
+    // into every plane step of a uint8 tile (302^3 5^3: 7000 cycles a step
+    // against 1536 of products) and made every second step wait for the loads
+    // it had just issued.
+    constexpr int NQ = C::NQ, QR = C::PITCH / 4;
     constexpr int NE4 = (NQ + kNT - 1) / kNT;
-    static_assert(C::PITCH % 4 == 0, "quads inside rows");
-    uint32_t goff[NE4][4];
-    uint32_t edge = 0;  // bit i: quad i takes four cell loads
+    static_assert(C::PITCH % 4 == 0 && R < 4, "quads inside rows, one left of cell 0");
+    static_assert(3 * C::HY <= kNT, "a face quad per thread");
+    const int xl = x0 - R;  // source column of staged column 0
+    const bool face = xl < 0 || xl + C::PITCH > a.X;
+    uint32_t goff[NE4];     // byte offset of the quad's 4-cell window
+    int qpos[NE4];          // its place in the staged plane
+    uint32_t inner = 0;     // bit i: quad i lies inside its row
+    const int32_t plane_cells = (int32_t)plane;
 #pragma unroll
     for (int i = 0; i < NE4; ++i) {
         const int e = min(t + i * kNT, NQ - 1);  // repeats the last quad (same values)
-        const int hy = (4 * e) / C::PITCH, hx = 4 * e - hy * C::PITCH;
+        const int hy = e / QR, hx = 4 * (e % QR);
+        qpos[i] = C::at(hy, hx);
         const int gy = addr_map((int64_t)y0 - R + hy, a.Y, a.mode);
-        const int xs = x0 - R + hx;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int gx = addr_map((int64_t)xs + j, a.X, a.mode);
-            // cells past the volume edge that only feed zero weights still
-            // read a finite value: clamp/wrap/mirror fetch them, border reads 0
-            goff[i][j] = (gx < 0 || gy < 0)
-                             ? kOutside
-                             : ((uint32_t)gy * (uint32_t)a.X + (uint32_t)gx) * (uint32_t)sizeof(T);
-        }
-        // (a row outside the volume under border mode reads 0 as a quad)
-        if (gy >= 0 && (xs < 0 || xs + 3 >= a.X)) edge |= 1u << i;
+        const int xs = xl + hx;
+        // (a face quad's load stays inside the plane, of at least 4 cells; it
+        // is not staged; a row outside the volume under border mode reads 0)
+        const int32_t cell = min(max(gy, 0) * a.X + max(xs, 0), plane_cells - 4);
+        goff[i] = gy < 0 ? kOutside : (uint32_t)cell * (uint32_t)sizeof(T);
+        if (xs >= 0 && xs + 3 < a.X) inner |= 1u << i;
     }
-    // cells of the planes in flight: slot p % PF holds plane p
-    T raw[C::PF][NE4][4];
-    auto gather = [&](auto slot, int zi) {
-        constexpr int S = decltype(slot)::value;
+    // this thread's face quad: byte offsets of its cells, its place in LDS
+    uint32_t foff[4];
+    int fe = -1;
+    if (face) {
+        const int q1 = (a.X - xl) / 4;  // the quad that holds column X
+        const int nl = xl < 0 ? 1 : 0;  // left quad 0, then right quads qr0 ...
+        const int qr0 = nl && q1 == 0 ? 1 : q1;
+        const int nr = (q1 < QR && qr0 == q1 ? 1 : 0) +
+                       (q1 + 1 < QR && 4 * (q1 + 1) < a.X + R - xl ? 1 : 0);
+        const int nf = nl + nr;
+        if (t < nf * C::HY) {
+            const int hy = t / nf, f = t - hy * nf;
+            const int qx = f < nl ? 0 : qr0 + f - nl;
+            const int gy = addr_map((int64_t)y0 - R + hy, a.Y, a.mode);
+            fe = C::at(hy, 4 * qx);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int gx = addr_map((int64_t)xl + 4 * qx + j, a.X, a.mode);
+                foff[j] = (gx < 0 || gy < 0)
+                              ? kOutside
+                              : ((uint32_t)gy * (uint32_t)a.X + (uint32_t)gx) * (uint32_t)sizeof(T);
+            }
+        }
+        for (int e = t; e < 2 * PC::PS * PLANE / 8; e += kNT)
+            reinterpret_cast<u32x4*>(lds_base)[e] = u32x4{0u, 0u, 0u, 0u};
+        __syncthreads();
+    }
+    // cells of the plane in flight (face cells in whole registers, so that no
+    // load has to be waited for to pack them)
+    using Tf = typename std::conditional<std::is_same<T, float>::value, float, uint32_t>::type;
+    T raw[NE4][4];
+    Tf fraw[4];
+    auto gather = [&](int zi) {
         const int gz = addr_map(zi, a.Z, a.mode);
         const char* base = reinterpret_cast<const char*>(a.src) +
                            (gz < 0 ? 0 : (int64_t)gz * plane_bytes);
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<char*>(base), (short)0, gz < 0 ? 0 : plane_bytes, (int)kRsrcWord3);
 #pragma unroll
-        for (int i = 0; i < NE4; ++i) {
-            if (edge & (1u << i)) {
+        for (int i = 0; i < NE4; ++i) buf_load4<T>(rs, goff[i], raw[i]);
+        if (face && fe >= 0) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) raw[S][i][j] = buf_load<T>(rs, goff[i][j]);
-            } else {
-                buf_load4<T>(rs, goff[i][0], raw[S][i]);
+            for (int j = 0; j < 4; ++j) fraw[j] = (Tf)buf_load<T>(rs, foff[j]);
+        }
+    };
+    auto put = [&](int buf) {
+        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+        auto stage = [&](const T (&v)[4], int e, bool on) {  // e: place of the quad's first cell
+            uint32_t p01[3], p23[3];
+            split_pair<PM>(v[0], v[1], p01);
+            split_pair<PM>(v[2], v[3], p23);
+            if (on) {
+#pragma unroll
+                for (int ps = 0; ps < PC::PS; ++ps)
+                    *reinterpret_cast<u32x2*>(&lds[buf][ps][e]) = u32x2{p01[ps], p23[ps]};
+            }
+        };
+        if (!face) {
+#pragma unroll
+            for (int i = 0; i < NE4; ++i) stage(raw[i], qpos[i], true);
+        } else {
+#pragma unroll
+            for (int i = 0; i < NE4; ++i)
+                stage(raw[i], qpos[i], (inner >> i) & 1u);
+            if (fe >= 0) {
+                const T v[4] = {(T)fraw[0], (T)fraw[1], (T)fraw[2], (T)fraw[3]};
+                stage(v, fe, true);
             }
         }
     };
-    auto put = [&](auto slot, auto buf) {
-        constexpr int S = decltype(slot)::value, BUF = decltype(buf)::value;
-#pragma unroll
-        for (int i = 0; i < NE4; ++i) {
-            const int e = min(t + i * kNT, NQ - 1);
-            uint32_t p01[3], p23[3];
-            split_pair<PM>(raw[S][i][0], raw[S][i][1], p01);
-            split_pair<PM>(raw[S][i][2], raw[S][i][3], p23);
-            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-            for (int ps = 0; ps < PC::PS; ++ps)
-                *reinterpret_cast<u32x2*>(&lds[BUF][ps][4 * e]) = u32x2{p01[ps], p23[ps]};
-        }
-    };
 
-    // ---- output: after the exchange lane l holds row 2 (l % 32) + l / 32 of
-    // the tile at the wave's 8 columns; the workgroup's 64 x 32 block goes
-    // through LDS (epi[P], double buffered) so that each row is stored by 4
-    // consecutive lanes, 8 cells each (whole 128-byte rows per 4 lanes)
-    const int erow = 2 * (lane % 32) + lane / 32;
-    const int srow = t / 4, scol = 8 * (t % 4);
-    const int ys = y0 + srow, xs8 = x0 + scol;
+    // ---- output: lane l holds row 2 (l % 32) + l / 32 of the tile at the
+    // wave's WX columns; the workgroup's block goes through LDS (epi[P],
+    // double buffered) so that each row is stored by 4 consecutive lanes, CP
+    // cells each (whole rows of the tile per 4 lanes)
+    constexpr int CP = C::TX / 4;
+    typedef float evec __attribute__((ext_vector_type(C::EV)));
+    const int srow = t / 4, scol = CP * (t % 4);
+    const int ys = y0 + srow, xst = x0 + scol;
     // rows past the region's last row fall beyond the plane: dropped
     const uint32_t ooff =
-        ys < a.ry1 ? ((uint32_t)ys * (uint32_t)a.X + (uint32_t)xs8) * (uint32_t)sizeof(T) : kOutside;
-    const bool vec_row = a.vec_ok && xs8 + 8 <= a.rx1;
+        ys < a.ry1 ? ((uint32_t)ys * (uint32_t)a.X + (uint32_t)xst) * (uint32_t)sizeof(T) : kOutside;
+    const bool vec_row = xst + CP <= a.rx1;  // (buffer stores take any cell alignment)
 
     f32x16 acc[C::WS];
 #pragma unroll
@@ -269,130 +358,134 @@ __device__ void rp_tile(const VolDesc& a, const float* __restrict__ w, int tile,
 
     // lane's B-operand row and first column inside the staged plane
     const int brow = 2 * (lane % 32) + lane / 32;
-    const int bcol = 8 * wave;
+    const int bcol = C::WX * wave, boff = C::at(brow, bcol);
 
     const int zi_beg = zb - R, zi_end = ze + R;
-    using S0 = std::integral_constant<int, 0>;
-    using S1 = std::integral_constant<int, 1>;
-    gather(S0{}, zi_beg);
-    if constexpr (C::PF == 2) gather(S1{}, min(zi_beg + 1, zi_end - 1));
-    put(S0{}, S0{});
+    gather(zi_beg);
+    put(0);
+    gather(min(zi_beg + 1, zi_end - 1));
     __syncthreads();
 
-    // One input plane zi; P = (zi - zi_beg) % 2 is its LDS buffer and its
-    // register slot.  The loads of plane zi + 2 go out first (into the slot
-    // plane zi has left), plane zi + 1 (loaded one plane earlier) is staged
-    // after the products.
-    auto step = [&](auto par, int zi) {
-        constexpr int P = decltype(par)::value;
-        // register slots of the plane loaded now and of the plane staged
-        // after the products
-        constexpr int LOAD = C::PF == 2 ? P : 0, STAGE = C::PF == 2 ? P ^ 1 : 0;
-        gather(std::integral_constant<int, LOAD>{}, min(zi + C::PF, zi_end - 1));
+    // One input plane zi = zi_beg + p, U = p mod k; LDS buffer cur holds it,
+    // the loads of plane zi + 1 are in flight.  That plane is staged after the
+    // products and the loads of plane zi + 2 take its registers at once, so
+    // that they have a whole step to arrive.  The loop is unrolled by k, which
+    // fixes the ring slot that a plane finishes: with a slot index in a
+    // register the compiler copied the accumulators for every indexed move.
+    int cur = 0;
+    auto step = [&](auto uc, int zi) __attribute__((always_inline)) {
+        constexpr int U = decltype(uc)::value;
 
-        // Row segments: lane (n, g) = (l % 32, l / 32) needs, in chunk q, the
-        // 16 cells from the wave's first column of staged row 2n + g + 2q,
-        // i.e. the row lane (n + 1, g) held in chunk q - 1.  Chunk 0 is read
-        // from LDS; chunk q + 1 is chunk q moved down one lane inside each
-        // 16-lane row (DPP row_shl:1), the last lane of each row reading its
-        // own row from LDS.  seg[ps][h]: dwords 4h .. 4h+3 of the segment.
-        auto read_seg = [&](int q, u32x4 (&sg)[PC::PS][2]) {
-            const int off = (brow + 2 * q) * C::PITCH + bcol;
+        // chunk q: lane (n, g) = (l % 32, l / 32) reads its weights and the
+        // cells from the wave's first column of staged row 2n + g + 2q on; the
+        // reads of chunk q + 1 go out before the products of chunk q
+        u16x8 W[2][PC::NBI];
+        uint32_t seg[2][PC::PS][C::SEGD];
+        auto load_chunk = [&](int q, u16x8 (&wq)[PC::NBI], uint32_t (&sg)[PC::PS][C::SEGD]) {
+#pragma unroll
+            for (int bi = 0; bi < PC::NBI; ++bi)
+                wq[bi] = *reinterpret_cast<const u16x8*>(
+                    &tab[aoff + (q * PC::NBI + bi) * 2 * C::AROWS * 8]);
+            const int off = boff + q * C::PAIR;
+            typedef uint32_t vrd __attribute__((ext_vector_type(C::RD)));
 #pragma unroll
             for (int ps = 0; ps < PC::PS; ++ps)
 #pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    sg[ps][h] = *reinterpret_cast<const u32x4*>(&lds[P][ps][off + 8 * h]);
+                for (int h = 0; h < C::SEGD / C::RD; ++h) {
+                    const vrd v = *reinterpret_cast<const vrd*>(&lds[cur][ps][off + 2 * C::RD * h]);
+#pragma unroll
+                    for (int d = 0; d < C::RD; ++d) sg[ps][C::RD * h + d] = v[d];
+                }
         };
-        u32x4 seg[2][PC::PS][2];
-        // the products at raised wave priority: the issue arbiter prefers
-        // this wave's matrix instructions over the other wave's staging and
-        // epilogue work (1024^3 7^3: 3.18 -> 3.08 ms)
+        // Raised wave priority, higher with each chunk: the wave that is ahead
+        // in its products takes the matrix cores and ends first, so that its
+        // staging and output run under the other wave's products.  At one
+        // priority the two waves of a SIMD share the matrix cores evenly, end
+        // together and then both leave them idle.
         __builtin_amdgcn_s_setprio(1);
-        read_seg(0, seg[0]);
+        load_chunk(0, W[0], seg[0]);
 #pragma unroll
         for (int q = 0; q < C::NCH; ++q) {
-            u32x4 (&cur)[PC::PS][2] = seg[q & 1];
-            u32x4 (&nxt)[PC::PS][2] = seg[(q + 1) & 1];
-            if (q + 1 < C::NCH) {
-                if ((lane & 15) == 15) read_seg(q + 1, nxt);
-            }
-            // strips outer, products inner (dependent 32x32x16 MFMAs issue
-            // back to back at full rate with two waves per SIMD), so only one
-            // strip window is live: dwords s .. s+3 of the segment
+            if (q == 1) __builtin_amdgcn_s_setprio(2);
+            if (q == C::NCH - 1) __builtin_amdgcn_s_setprio(3);
+            if (q + 1 < C::NCH) load_chunk(q + 1, W[(q + 1) & 1], seg[(q + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+            // two strips at a time (their windows' registers), products outer:
+            // consecutive products are independent
 #pragma unroll
-            for (int st = 0; st < C::WS; ++st) {
-                u32x4 B[PC::PS];
+            for (int s0 = 0; s0 < C::WS; s0 += 2) {
+                u32x4 B[2][PC::PS];  // the 8 cells from column NX st of the segment on
 #pragma unroll
-                for (int ps = 0; ps < PC::PS; ++ps)
+                for (int s1 = 0; s1 < 2; ++s1)
 #pragma unroll
-                    for (int d = 0; d < 4; ++d) B[ps][d] = cur[ps][(st + d) / 4][(st + d) % 4];
+                    for (int ps = 0; ps < PC::PS; ++ps)
+#pragma unroll
+                        for (int d = 0; d < 4; ++d) {
+                            const uint32_t(&sg)[C::SEGD] = seg[q & 1][ps];
+                            const int st = s0 + s1, d0 = C::NX * st / 2 + d;
+                            B[s1][ps][d] = C::NX * st % 2
+                                               ? __builtin_amdgcn_alignbit(sg[d0 + 1], sg[d0], 16)
+                                               : sg[d0];
+                        }
 #pragma unroll
                 for (int pr = 0; pr < PC::NPROD; ++pr)
-                    acc[st] = mfma32<PC::F16>(W[q][PC::prod[pr][1]], B[PC::prod[pr][0]], acc[st]);
+#pragma unroll
+                    for (int s1 = 0; s1 < 2; ++s1)
+                        acc[s0 + s1] = mfma32<PC::F16>(W[q & 1][PC::prod[pr][1]],
+                                                       B[s1][PC::prod[pr][0]], acc[s0 + s1]);
+                if (C::NX == 3) __builtin_amdgcn_sched_barrier(0);
             }
-            // next chunk's segment (after this chunk's products, so the
-            // patch reads have landed)
-            if (q + 1 < C::NCH) {
-#pragma unroll
-                for (int ps = 0; ps < PC::PS; ++ps)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h)
-#pragma unroll
-                        for (int d = 0; d < 4; ++d)
-                            nxt[ps][h][d] = (uint32_t)__builtin_amdgcn_update_dpp(
-                                (int)nxt[ps][h][d], (int)cur[ps][h][d], 0x101, 0xf, 0xf, false);
-            }
+            __builtin_amdgcn_sched_barrier(0);
         }
+        aoff = aoff == alast ? afirst : aoff + ASTEP;
         // the next plane's cells are split and staged after the products
         __builtin_amdgcn_s_setprio(0);
         __builtin_amdgcn_sched_barrier(0);
-        put(std::integral_constant<int, STAGE>{}, std::integral_constant<int, P ^ 1>{});
+        put(cur ^ 1);
+        gather(min(zi + 2, zi_end - 1));
 
-        // ---- registers RFIN, RFIN + 1 hold output plane zi - r
+        // ---- ring slot U + 1 holds output plane zi - r; it restarts at zero
+        constexpr int done = (U + 1) % K;
         const int zo = zi - R;
         const bool out = zo >= zb;
-        if (out) {
-            float v[8];
+        float fin[C::WX];
 #pragma unroll
-            for (int st = 0; st < C::WS; ++st) {
-                // (element values taken by value: a bit cast of a vector
-                // element reference reads element 0 with this compiler)
-                const float f0 = acc[st][C::RFIN], f1 = acc[st][C::RFIN + 1];
-                const auto pq = __builtin_amdgcn_permlane32_swap(__float_as_uint(f0),
-                                                                 __float_as_uint(f1), false, false);
-                v[2 * st] = __uint_as_float((uint32_t)pq[0]);      // column 2 st
-                v[2 * st + 1] = __uint_as_float((uint32_t)pq[1]);  // column 2 st + 1
+        for (int st = 0; st < C::WS; ++st)
+#pragma unroll
+            for (int xo = 0; xo < C::NX; ++xo) {
+                fin[C::NX * st + xo] = acc[st][C::NX * done + xo];
+                acc[st][C::NX * done + xo] = 0.f;
             }
-            float* e = &epi[P][erow][8 * wave];
-            *reinterpret_cast<f32x4*>(e) = f32x4{v[0], v[1], v[2], v[3]};
-            *reinterpret_cast<f32x4*>(e + 4) = f32x4{v[4], v[5], v[6], v[7]};
-        }
-        // ---- advance the ring: filter plane c -> c + 1 is register r -> r + 2
+        if (out) {
 #pragma unroll
-        for (int st = 0; st < C::WS; ++st) {
+            for (int h = 0; h < C::WX / C::EV; ++h) {
+                evec v;
 #pragma unroll
-            for (int r = 2 * K - 1; r >= 2; --r) acc[st][r] = acc[st][r - 2];
-            acc[st][0] = 0.f;
-            acc[st][1] = 0.f;
+                for (int d = 0; d < C::EV; ++d) v[d] = fin[C::EV * h + d];
+                *reinterpret_cast<evec*>(&epi[cur][brow][bcol + C::EV * h]) = v;
+            }
         }
         // the next plane (staged above) and this plane's outputs are complete
         __syncthreads();
         if (out) {
-            const float* e = &epi[P][srow][scol];
-            const f32x4 lo = *reinterpret_cast<const f32x4*>(e);
-            const f32x4 hi = *reinterpret_cast<const f32x4*>(e + 4);
-            const float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            float v[CP];
+#pragma unroll
+            for (int h = 0; h < CP / C::EV; ++h) {
+                const evec u = *reinterpret_cast<const evec*>(&epi[cur][srow][scol + C::EV * h]);
+#pragma unroll
+                for (int d = 0; d < C::EV; ++d) v[C::EV * h + d] = u[d];
+            }
             const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
                 static_cast<char*>(a.dst) + (int64_t)zo * plane_bytes, (short)0, plane_bytes,
                 (int)kRsrcWord3);
-            store_row<T, 8>(rd, ooff, v, vec_row, a.rx1 - xs8, a.unscale);
+            store_row<T, CP>(rd, ooff, v, vec_row, a.rx1 - xst, a.unscale);
         }
+        cur ^= 1;
     };
-    for (int zi = zi_beg; zi < zi_end; zi += 2) {
-        step(S0{}, zi);
-        if (zi + 1 < zi_end) step(S1{}, zi + 1);
-    }
+    for (int zi = zi_beg; zi < zi_end; zi += K)
+        static_for<K>([&](auto uc) __attribute__((always_inline)) {
+            if (zi + decltype(uc)::value < zi_end) step(uc, zi + decltype(uc)::value);
+        });
 }
 
 template <class C>
@@ -406,10 +499,11 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(2)))
 void filter_mfma_rp_kernel(VolDesc a, const float* __restrict__ w, uint32_t nblocks)
 {
     __shared__ __align__(16) uint16_t lds[rp_lds_elems<C>()];
-    __shared__ __align__(16) float epi[2][64][kEpiPitch];
+    __shared__ __align__(16) float epi[2][C::TY][C::EPITCH];
+    __shared__ __align__(16) uint16_t tab[C::TABLE];
     const uint32_t lid = xcd_remap(blockIdx.x, nblocks);
     const uint32_t ntiles = (uint32_t)a.tiles_x * (uint32_t)a.tiles_y;
-    rp_tile<C>(a, w, (int)(lid % ntiles), (int)(lid / ntiles), lds, epi);
+    rp_tile<C>(a, w, (int)(lid % ntiles), (int)(lid / ntiles), lds, epi, tab);
 }
 
 // Persistent workgroups over a queue of (volume, tile-slab) items; the last
@@ -419,7 +513,8 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(2)))
 void filter_mfma_rp_batched_kernel(BatchArgs b)
 {
     __shared__ __align__(16) uint16_t lds[rp_lds_elems<C>()];
-    __shared__ __align__(16) float epi[2][64][kEpiPitch];
+    __shared__ __align__(16) float epi[2][C::TY][C::EPITCH];
+    __shared__ __align__(16) uint16_t tab[C::TABLE];
     __shared__ uint32_t s_item;
     for (;;) {
         if (threadIdx.x == 0) s_item = atomicAdd(&b.counters[0], 1u);
@@ -432,7 +527,7 @@ void filter_mfma_rp_batched_kernel(BatchArgs b)
         const WorkItem wi = uniform_load(&b.items[it]);
         const VolDesc a = uniform_load(&b.vols[wi.vol]);
         const uint32_t ntiles = (uint32_t)a.tiles_x * (uint32_t)a.tiles_y;
-        rp_tile<C>(a, b.wpool + a.woff, (int)(wi.lid % ntiles), (int)(wi.lid / ntiles), lds, epi);
+        rp_tile<C>(a, b.wpool + a.woff, (int)(wi.lid % ntiles), (int)(wi.lid / ntiles), lds, epi, tab);
         // the next item's staging reuses the LDS buffers
         __syncthreads();
     }
@@ -479,9 +574,9 @@ hipError_t rp_launch(const FilterJob& j, hipStream_t s)
 template <typename T, int PM>
 hipError_t rp_dispatch(const FilterJob& j, hipStream_t s)
 {
-    switch (j.k) {
-    case 5: return rp_launch<RpCfg<T, 5, PM>>(j, s);
-    case 7: return rp_launch<RpCfg<T, 7, PM>>(j, s);
+    if (j.k == 5) return rp_launch<RpCfg<T, 5, PM>>(j, s);
+    if constexpr (PM == kF32x3) {
+        if (j.k == 7) return rp_launch<RpCfg<T, 7, PM>>(j, s);
     }
     return hipErrorInvalidValue;
 }
@@ -489,9 +584,9 @@ hipError_t rp_dispatch(const FilterJob& j, hipStream_t s)
 template <typename T, int PM>
 const void* rp_batched(int k)
 {
-    switch (k) {
-    case 5: return (const void*)&filter_mfma_rp_batched_kernel<RpCfg<T, 5, PM>>;
-    case 7: return (const void*)&filter_mfma_rp_batched_kernel<RpCfg<T, 7, PM>>;
+    if (k == 5) return (const void*)&filter_mfma_rp_batched_kernel<RpCfg<T, 5, PM>>;
+    if constexpr (PM == kF32x3) {
+        if (k == 7) return (const void*)&filter_mfma_rp_batched_kernel<RpCfg<T, 7, PM>>;
     }
     return nullptr;
 }
@@ -499,9 +594,9 @@ const void* rp_batched(int k)
 template <typename T, int PM>
 ClassGeom rp_geom_k(int k)
 {
-    switch (k) {
-    case 5: return rp_geom<RpCfg<T, 5, PM>>();
-    case 7: return rp_geom<RpCfg<T, 7, PM>>();
+    if (k == 5) return rp_geom<RpCfg<T, 5, PM>>();
+    if constexpr (PM == kF32x3) {
+        if (k == 7) return rp_geom<RpCfg<T, 7, PM>>();
     }
     return ClassGeom{};
 }

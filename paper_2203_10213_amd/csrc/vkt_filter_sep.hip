@@ -55,23 +55,6 @@ struct GeoS {
 constexpr uint32_t kRsrcWord3 = 0x00020000u;  // gfx9-family raw buffer
 constexpr uint32_t kOutside = 0x80000000u;    // byte offset that reads 0
 
-__device__ inline int addr_map(int64_t i, int64_t n, int mode)
-{
-    if (i >= 0 && i < n) return (int)i;
-    if (mode == vktAddressModeClamp) return i < 0 ? 0 : (int)(n - 1);
-    if (mode == vktAddressModeWrap) {
-        int64_t m = i % n;
-        return (int)(m < 0 ? m + n : m);
-    }
-    if (mode == vktAddressModeMirror) {
-        const int64_t p = 2 * n;
-        int64_t m = i % p;
-        if (m < 0) m += p;
-        return (int)(m < n ? m : p - 1 - m);
-    }
-    return -1;
-}
-
 __device__ inline uint32_t xcd_remap(uint32_t b, uint32_t n)
 {
     const uint32_t q = n / 8, rem = n % 8, xcd = b % 8, idx = b / 8;

@@ -66,24 +66,6 @@ struct Geo {
     static_assert(4 * (kBX - 1) + 4 * NR <= P, "row window exceeds LDS pitch");
 };
 
-// Address mode on one axis; -1 means "outside, reads zero" (border).
-__device__ inline int addr_map(int64_t i, int64_t n, int mode)
-{
-    if (i >= 0 && i < n) return (int)i;
-    if (mode == vktAddressModeClamp) return i < 0 ? 0 : (int)(n - 1);
-    if (mode == vktAddressModeWrap) {
-        int64_t m = i % n;
-        return (int)(m < 0 ? m + n : m);
-    }
-    if (mode == vktAddressModeMirror) {
-        const int64_t p = 2 * n;
-        int64_t m = i % p;
-        if (m < 0) m += p;
-        return (int)(m < n ? m : p - 1 - m);
-    }
-    return -1;
-}
-
 // Workgroup id -> logical tile id such that consecutive logical ids land on
 // the same XCD (the dispatcher deals workgroups to the 8 XCDs round-robin).
 __device__ inline uint32_t xcd_remap(uint32_t b, uint32_t n)

@@ -137,6 +137,26 @@ struct WorkItem {
     uint32_t lid;            // slab * tiles_x * tiles_y + tile
 };
 
+// Address mode on one axis of n cells: the cell that position i reads; -1
+// means "outside, reads zero" (border).  Positions before the volume are
+// folded to their distance from cell 0 (-1 - i), so that the periods divide
+// as 32-bit numbers (a 64-bit remainder is a call of some 150 instructions).
+__device__ inline int addr_map(int64_t i, int32_t n, int mode)
+{
+    if (i >= 0 && i < n) return (int)i;
+    if (mode == vktAddressModeClamp) return i < 0 ? 0 : n - 1;
+    const uint32_t u = (uint32_t)(i < 0 ? -1 - i : i);
+    if (mode == vktAddressModeWrap) {
+        const int m = (int)(u % (uint32_t)n);
+        return i < 0 ? n - 1 - m : m;
+    }
+    if (mode == vktAddressModeMirror) {
+        const uint32_t m = u % (2u * (uint32_t)n);  // (mirrored about cell 0's edge: i and -1 - i)
+        return (int)(m < (uint32_t)n ? m : 2u * (uint32_t)n - 1u - m);
+    }
+    return -1;
+}
+
 // *p as a wave-uniform value: each dword is read by every lane and taken from
 // the first, so the struct (written by the host before the launch) lives in
 // scalar registers instead of one copy per lane.

@@ -55,23 +55,6 @@ template <> struct Pieces<kF32x6> {
     static constexpr int prod[NPROD][2] = {{0, 0}, {0, 1}, {1, 0}, {0, 2}, {1, 1}, {2, 0}};
 };
 
-__device__ inline int addr_map(int64_t i, int64_t n, int mode)
-{
-    if (i >= 0 && i < n) return (int)i;
-    if (mode == vktAddressModeClamp) return i < 0 ? 0 : (int)(n - 1);
-    if (mode == vktAddressModeWrap) {
-        int64_t m = i % n;
-        return (int)(m < 0 ? m + n : m);
-    }
-    if (mode == vktAddressModeMirror) {
-        const int64_t p = 2 * n;
-        int64_t m = i % p;
-        if (m < 0) m += p;
-        return (int)(m < n ? m : p - 1 - m);
-    }
-    return -1;
-}
-
 __device__ inline uint32_t xcd_remap(uint32_t b, uint32_t n)
 {
     const uint32_t q = n / 8, rem = n % 8, xcd = b % 8, idx = b / 8;
@@ -130,80 +113,73 @@ __device__ inline void split_weight(float w, float scale, uint16_t* p)
     }
 }
 
+// W consecutive dwords at byte offset off, in as few stores as there are.
+template <int W>
+__device__ inline void store_dwords(__amdgpu_buffer_rsrc_t r, uint32_t off, const uint32_t (&u)[W])
+{
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
+    constexpr int Q = W / 4;
+#pragma unroll
+    for (int h = 0; h < Q; ++h)
+        __builtin_amdgcn_raw_buffer_store_b128(
+            u32x4{u[4 * h], u[4 * h + 1], u[4 * h + 2], u[4 * h + 3]}, r, (int)off + 16 * h, 0, 0);
+    if constexpr (W % 4 == 3)
+        __builtin_amdgcn_raw_buffer_store_b96(u32x3{u[4 * Q], u[4 * Q + 1], u[4 * Q + 2]}, r,
+                                              (int)off + 16 * Q, 0, 0);
+    else if constexpr (W % 4 == 2)
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2{u[4 * Q], u[4 * Q + 1]}, r, (int)off + 16 * Q, 0,
+                                              0);
+    else if constexpr (W % 4 == 1)
+        __builtin_amdgcn_raw_buffer_store_b32(u[4 * Q], r, (int)off + 16 * Q, 0, 0);
+}
+
 // Round (integer cells) and store one lane's row of N finished outputs at
-// byte offset off: one vector store when the row lies inside the volume and
-// is 4-byte aligned, else cell stores for the first nx cells.  Dropped rows
-// carry an out-of-range offset.
+// byte offset off: vector stores when the row lies inside the volume (buffer
+// stores take any cell alignment), else cell stores for the first nx cells.
+// Dropped rows carry an out-of-range offset.
 template <typename T, int N>
 __device__ inline void store_row(__amdgpu_buffer_rsrc_t r, uint32_t off, const float (&v)[N],
                                  bool vec, int nx, float unscale)
 {
-    static_assert(N == 8 || N == 4 || N == 2, "rows of 8, 4 or 2 cells");
+    uint32_t u[N];
     if constexpr (std::is_same<T, float>::value) {
-        uint32_t u[N];
 #pragma unroll
         for (int i = 0; i < N; ++i) u[i] = __float_as_uint(v[i] * unscale);
-        if (vec) {
-            if constexpr (N == 2) {
-                typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-                __builtin_amdgcn_raw_buffer_store_b64(u32x2{u[0], u[1]}, r, (int)off, 0, 0);
-            } else {
-#pragma unroll
-                for (int h = 0; h < N / 4; ++h)
-                    __builtin_amdgcn_raw_buffer_store_b128(
-                        u32x4{u[4 * h], u[4 * h + 1], u[4 * h + 2], u[4 * h + 3]}, r,
-                        (int)off + 16 * h, 0, 0);
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < N; ++i)
-                __builtin_amdgcn_raw_buffer_store_b32(u[i], r, i < nx ? (int)(off + 4 * i) : (int)kOutside,
-                                                      0, 0);
-        }
     } else {
         constexpr float kMax = std::is_same<T, uint8_t>::value ? 255.f : 65535.f;
-        uint32_t u[N];
 #pragma unroll
         for (int i = 0; i < N; ++i)
             // floor(q + 1/2) saturated: truncation of a value clamped to [0, max]
             u[i] = (uint32_t)__builtin_amdgcn_fmed3f(fmaf(v[i], unscale, 0.5f), 0.f, kMax);
-        if (vec) {
-            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-            if constexpr (sizeof(T) == 2 && N == 8) {
-                __builtin_amdgcn_raw_buffer_store_b128(
-                    u32x4{u[0] | (u[1] << 16), u[2] | (u[3] << 16), u[4] | (u[5] << 16),
-                          u[6] | (u[7] << 16)},
-                    r, (int)off, 0, 0);
-            } else if constexpr (sizeof(T) == 2 && N == 4) {
-                __builtin_amdgcn_raw_buffer_store_b64(
-                    u32x2{u[0] | (u[1] << 16), u[2] | (u[3] << 16)}, r, (int)off, 0, 0);
-            } else if constexpr (sizeof(T) == 2) {
-                __builtin_amdgcn_raw_buffer_store_b32(u[0] | (u[1] << 16), r, (int)off, 0, 0);
-            } else if constexpr (N == 8) {
-                __builtin_amdgcn_raw_buffer_store_b64(
-                    u32x2{u[0] | (u[1] << 8) | (u[2] << 16) | (u[3] << 24),
-                          u[4] | (u[5] << 8) | (u[6] << 16) | (u[7] << 24)},
-                    r, (int)off, 0, 0);
-            } else if constexpr (N == 4) {
-                __builtin_amdgcn_raw_buffer_store_b32(u[0] | (u[1] << 8) | (u[2] << 16) | (u[3] << 24),
-                                                      r, (int)off, 0, 0);
-            } else {
-                __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(u[0] | (u[1] << 8)), r, (int)off,
-                                                      0, 0);
-            }
+    }
+    if (vec) {
+        constexpr int CPD = 4 / sizeof(T);  // cells per dword
+        if constexpr (N < CPD) {
+            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(u[0] | (u[1] << 8)), r, (int)off, 0, 0);
         } else {
+            uint32_t d[N / CPD];
 #pragma unroll
-            for (int i = 0; i < N; ++i) {
-                const int o = i < nx ? (int)(off + sizeof(T) * i) : (int)kOutside;
-                if constexpr (sizeof(T) == 2)
-                    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)u[i], r, o, 0, 0);
-                else
-                    __builtin_amdgcn_raw_buffer_store_b8((uint8_t)u[i], r, o, 0, 0);
+            for (int i = 0; i < N / CPD; ++i) {
+                d[i] = u[CPD * i];
+#pragma unroll
+                for (int c = 1; c < CPD; ++c) d[i] |= u[CPD * i + c] << (8 * sizeof(T) * c);
             }
+            store_dwords<N / CPD>(r, off, d);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int o = i < nx ? (int)(off + sizeof(T) * i) : (int)kOutside;
+            if constexpr (sizeof(T) == 4)
+                __builtin_amdgcn_raw_buffer_store_b32(u[i], r, o, 0, 0);
+            else if constexpr (sizeof(T) == 2)
+                __builtin_amdgcn_raw_buffer_store_b16((uint16_t)u[i], r, o, 0, 0);
+            else
+                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)u[i], r, o, 0, 0);
         }
     }
 }
-
 
 }  // namespace
 }  // namespace vkt
