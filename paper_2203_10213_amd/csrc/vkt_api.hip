@@ -543,8 +543,7 @@ bool mfma_row_pairs(const FilterJob& j, bool six_products)
     const int64_t cells =
         (int64_t)(j.roi[3] - j.roi[0]) * (j.roi[4] - j.roi[1]) * (j.roi[5] - j.roi[2]);
     return (j.k == 5 || (j.k == 7 && j.fmt == vktDataFormatFloat32 && !six_products)) &&
-           cells > state().row_pair_min_cells &&
-           (int64_t)j.X * j.Y >= 4;  // (its staging loads 4-cell windows of a plane)
+           cells > state().row_pair_min_cells;
 }
 
 hipError_t launch_filter_mfma(const FilterJob& j, bool six_products, hipStream_t s)
@@ -569,6 +568,16 @@ ClassGeom mfma_geom(vktDataFormat f, int k, bool six_products, bool row_pairs, i
                      : mfma_geom_s16(f, k, six_products, variant);
 }
 
+int device_cus()
+{
+    int dev = 0, cus = 0;
+    (void)hipGetDevice(&dev);
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus < 1)
+        cus = 1;
+    return cus;
+}
+
 int resident_wgs(const void* func)
 {
     static std::mutex mu;
@@ -578,14 +587,11 @@ int resident_wgs(const void* func)
     std::lock_guard<std::mutex> lk(mu);
     auto it = cache.find({func, dev});
     if (it != cache.end()) return it->second;
-    int per_cu = 0, cus = 0;
+    int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, func, 256, 0) != hipSuccess ||
         per_cu < 1)
         per_cu = 1;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cus < 1)
-        cus = 1;
-    const int n = per_cu * cus;
+    const int n = per_cu * device_cus();
     cache[{func, dev}] = n;
     return n;
 }

@@ -9,8 +9,8 @@
 //   T(x,y,z) = sum_{a,b,c} w[a + k(b + k c)] * s(A(x+a-r), A(y+b-r), A(z+c-r)).
 //
 // GEMM embedding, per input plane zi (D += A * B on MFMA tiles):
-//   M (rows i)    : consecutive output rows y_i of one x-strip of NX = 2
-//                   output columns,
+//   M (rows i)    : consecutive output rows y_i of one x-strip of NX output
+//                   columns (3 for k = 5 and float32 k = 9, else 2),
 //   K (reduction) : (filter row b, input column ax) pairs; the A operand is
 //                   the input window s(x_s - r + ax, y_i + b - r, zi), read
 //                   straight from the LDS-staged plane (no im2col copy),
@@ -19,19 +19,29 @@
 //                   of each filter row, zero outside 0 <= ax - xo < k).
 // Column group c of D therefore accumulates the contribution of input plane
 // zi to output plane zi - c + r: the k output planes an input plane feeds
-// live side by side in D (a z ring).  After each input plane the group
-// c = k-1 holds a finished output plane; it is stored and the columns shift
-// by NX lanes (group c -> c+1, group 0 restarts at zero).
+// live side by side in D (a z ring).  On 16x16 tiles the finished group
+// c = k-1 is stored after each plane and the columns shift by NX lanes.  On
+// 32x32 tiles the accumulators stay (group s holds output plane s mod k of the
+// slab) and the weights turn: a lane reads the weights of the next filter
+// plane from a table in LDS.  Moving them instead took 64 ds_bpermute a plane
+// and wave behind the last product and kept the weights in registers (11^3
+// uint16 224 registers, now 156; 1024^3 15.25 -> 14.85 ms, 400x380x360 13^3
+// 1.15 -> 1.06 ms, 200x190x181 float32 15^3 with 6 products 484 -> 429 us).
 //
-// The four x-strips a wave owns are adjacent, so one 32-byte LDS read per
-// (row block, K chunk, operand piece) holds all four strips' 16-byte windows
-// (at dword offsets 0..3).  The finished column group of all of a wave's
-// tiles is an 8 x 32 (16x16 tiles) or 8 x 64 (32x32) block of outputs; it is
-// transposed through LDS so that each lane rounds and stores 4 or 8 cells of
-// one row with one vector store.
+// The four x-strips a wave owns are adjacent, so one segment read per (row
+// block, K chunk, operand piece) holds all their 16-byte windows.  With three
+// columns a strip the k = 5 tiles fill 15 of 16 columns instead of 10: a third
+// fewer products.  (The sum of 8 adjacent reduction slots does not depend on
+// their order -- checked on the GPU with permuted slots -- so that this changes
+// no result where a filter row lies in one such group, k <= 7; float32 k = 9
+// rounds differently.)  The finished column group of all of a wave's tiles is
+// transposed through LDS so that each lane rounds and stores adjacent cells of
+// one row.
 //
 // Operand splitting: see vkt_mfma_common.h.
 #include "vkt_mfma_common.h"
+
+#include <algorithm>
 
 #ifndef VKT_MFMA_SHAPE
 #error "compile with -DVKT_MFMA_SHAPE=16 or 32"
@@ -61,26 +71,17 @@ struct Cfg {
     static constexpr int SHAPE = K <= 7 ? 16 : 32;
     using M = Mf<SHAPE>;
     static constexpr int R = (K - 1) / 2;
-    static constexpr int NX = 2;                                    // output x per strip
+    // output columns per strip
+    static constexpr int NX = K == 5 || (K == 9 && std::is_same<T, float>::value) ? 3 : 2;
     static_assert(K * NX <= M::NT, "column groups exceed the tile");
     static_assert(NX + K - 1 <= M::AXW, "x window exceeds the K slots");
     static constexpr int NCH = SHAPE == 16 ? (K + 3) / 4 : K;      // K chunks
     static constexpr int SX = 16;                                   // strips per workgroup
     static constexpr int WS = 4;                                    // strips per wave
     static_assert(SX == 4 * WS, "four waves");
-    // row blocks per workgroup: 2 for both shapes (16x16 tiles with 4 row
-    // blocks needed a third more registers, two waves per SIMD instead of
-    // three or four, and measured 5-8 % slower)
-    // (32x32 tiles: one row block where that brings the kernel down to two
-    // waves per SIMD -- 9^3 with uint8 or 3-product float32 operands, 21 %
-    // faster on the 1024^3 9^3 workload, and, with the accumulators in
-    // VGPRs, every k >= 9 except 6-product float32 with k >= 13:
-    // 2048x2048x1024 11^3 uint16 71.5 -> 53.9 ms, 512^3 k = 11 / 13 / 15
-    // uint8 1.78 / 1.70 / 1.92 -> 1.34 / 1.35 / 1.67 ms, 512^3 9^3 uint16
-    // 2.30 -> 2.02 ms, 1024^3 9^3 six products 22.7 -> 20.6 ms; 6-product
-    // 13^3 and 15^3 would spill 37 and 61 registers there and keep the taller
-    // tile at one wave)
-    static constexpr bool ONE_BLOCK = SHAPE == 32 && (PM != kF32x6 || K <= 11);
+    // row blocks per workgroup: two 16-row blocks (with four the kernels
+    // needed a third more registers, two waves per SIMD instead of three or
+    // four, and measured 5-8 % slower), one 32-row block
     // segment reads of the next (row block, K chunk) group issued before the
     // current group's products: on 16x16 tiles, for uint16 and for 3-product
     // float32 9^3 (224 registers, no spills; 1024^3 12.45 -> 11.77 ms, 512^3
@@ -89,18 +90,28 @@ struct Cfg {
     // slower pipelined, float32 11^3 the same, and 6-product float32 spills.
     static constexpr bool PIPE = SHAPE == 16 || std::is_same<T, uint16_t>::value ||
                                  (std::is_same<T, float>::value && PM != kF32x6 && K <= 9);
-    static constexpr int SY_DEFAULT = SHAPE == 16 ? 2 : (ONE_BLOCK ? 1 : 2);
+    static constexpr int SY_DEFAULT = SHAPE == 16 ? 2 : 1;
     static constexpr int SY = SYV ? SYV : SY_DEFAULT;
     static constexpr int TX = SX * NX, TY = SY * M::MT;             // 32 x 32 or 32 x 64 tile
-    // a lane's 8-column windows of the wave's WS strips span SEGN columns,
-    // read as NRD 16-byte pieces
-    static constexpr int SEGN = NX * (WS - 1) + 8;
-    static constexpr int NRD = (SEGN + 7) / 8;
-    static constexpr int PITCH = SHAPE == 16 ? 40 : 48;             // row pitch (cells)
-    static_assert(PITCH % 8 == 0, "16-byte aligned rows");
-    static_assert(NX * WS * 3 + (SHAPE == 16 ? 0 : 8) + 8 * NRD <= PITCH, "pitch too small");
+    static constexpr int WX = WS * NX;                              // columns per wave
+    // dwords of a lane's segment: the 8-column windows of the wave's strips,
+    // read 8 bytes (24-byte wave offsets) or 16 bytes at a time
+    static constexpr int RD = WX % 8 == 0 ? 4 : 2;
+    static constexpr int SEGD = ((NX * (WS - 1) + 8 + 1) / 2 + RD - 1) / RD * RD;
+    // staged columns, and the row pitch that spreads the segment reads of
+    // consecutive rows over the LDS banks (an odd number of reads)
+    static constexpr int COLS = (3 * WX + (SHAPE == 16 ? 0 : 8) + 2 * SEGD + 7) / 8 * 8;
+    static constexpr int PITCH = RD == 2 ? (COLS % 8 == 0 ? COLS + 4 : COLS) : COLS;
+    static_assert(TX + K - 1 <= COLS && PITCH * 2 % (4 * RD) == 0, "staged columns");
     static constexpr int HY = TY + K - 1;                           // staged rows
-    static constexpr int NE = (PITCH * HY + kNT - 1) / kNT;         // staged cells / thread
+    static constexpr int PLANE = (HY * PITCH + 7) / 8 * 8;
+    static __device__ constexpr int at(int row, int col) { return row * PITCH + col; }
+    // 32x32 tiles: weight table in LDS, per (chunk, piece, lane half) the
+    // 16-byte rows of (c, xo), then a zero row for the unused columns
+    static constexpr int BROWS = K * NX + 1;
+    static constexpr int TABLE = SHAPE == 16 ? 8 : NCH * PC::NBI * 2 * BROWS * 8;
+    // output block of a wave: WX x BY cells, CPL of a row per lane
+    static constexpr int BY = SY * M::MT, CPL = WX * BY / 64;
     static constexpr int MTW = WS * SY;                             // M tiles per wave
     // waves per SIMD the single-volume kernel is compiled for: 16x16 tiles
     // with uint8 or 3-product float32 operands fit 128 registers (four
@@ -110,7 +121,7 @@ struct Cfg {
     // uint16 and 11^3 six-product float32 spill 14 and 15, and measured
     // faster or no slower)
     static constexpr int WAVES =
-        SHAPE == 16 ? (PM == kU8 || PM == kF32x3 ? 4 : 3) : (ONE_BLOCK ? 2 : 1);
+        SHAPE == 16 ? (PM == kU8 || PM == kF32x3 ? 4 : 3) : 2;
     // the persistent batched kernels need more registers: three waves for
     // the 16-bit operand classes, the float32 classes as they come
     static constexpr int BWAVES = SHAPE == 16 && (PM == kU8 || PM == kU16) ? 3 : 1;
@@ -136,26 +147,19 @@ __device__ inline typename Mf<SHAPE>::acc_t mfma(u32x4 a, u16x8 b, typename Mf<S
     }
 }
 
-// Shift the accumulator columns right by NX lanes inside each NT-wide column
-// group of lanes; the first NX columns become zero.
-template <int SHAPE, int NX>
-__device__ inline float shift_cols(float v, int lane)
+// Shift the accumulator columns of a 16x16 tile right by NX lanes; the first
+// NX columns become zero (DPP row_shr:NX inside each row of 16 lanes;
+// bound_ctrl writes 0).
+template <int NX>
+__device__ inline float shift_cols(float v)
 {
-    if constexpr (SHAPE == 16) {
-        // DPP row_shr:NX inside each row of 16 lanes; bound_ctrl writes 0
-        return __builtin_bit_cast(
-            float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x110 + NX, 0xf,
-                                               0xf, true));
-    } else {
-        const int src = lane - NX;
-        const int r = __builtin_amdgcn_ds_bpermute(src < 0 ? 0 : src * 4, __builtin_bit_cast(int, v));
-        return (lane % 32) < NX ? 0.f : __builtin_bit_cast(float, r);
-    }
+    return __builtin_bit_cast(
+        float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x110 + NX, 0xf, 0xf, true));
 }
 
 template <class C>
 __device__ void mfma_tile(const VolDesc& a, const float* __restrict__ w, int tile, int slab,
-                          uint16_t* lds_base, float* epi)
+                          uint16_t* lds_base, float* epi, uint16_t* tab)
 {
     using T = typename C::Tin;
     using PC = typename C::PC;
@@ -163,98 +167,86 @@ __device__ void mfma_tile(const VolDesc& a, const float* __restrict__ w, int til
     using acc_t = typename M::acc_t;
     constexpr int K = (C::R * 2) + 1;
     constexpr int R = C::R;
+    constexpr int NX = C::NX;
     constexpr int PM = std::is_same<T, uint8_t>::value ? kU8
                        : std::is_same<T, uint16_t>::value ? kU16
                        : (PC::NPROD == 6 ? kF32x6 : kF32x3);
-    auto lds = reinterpret_cast<uint16_t(*)[PC::PS][C::HY * C::PITCH]>(lds_base);
-    const T* __restrict__ src = static_cast<const T*>(a.src);
+    constexpr bool TURN = C::SHAPE == 32;  // the weights turn, the accumulators stay
+    // lds[buffer][piece][C::at(row, column)]
+    auto lds = reinterpret_cast<uint16_t(*)[PC::PS][C::PLANE]>(lds_base);
 
     const int t = threadIdx.x, lane = t % 64, wave = t / 64;
     const int x0 = a.rx0 + (tile % a.tiles_x) * C::TX, y0 = a.ry0 + (tile / a.tiles_x) * C::TY;
     const int zb = a.rz0 + slab * a.tz, ze = min(zb + a.tz, a.rz1);
     const int64_t plane = (int64_t)a.X * a.Y;
     const int32_t plane_bytes = (int32_t)(plane * (int64_t)sizeof(T));  // < 2^31 (host check)
-
-    // ---- B operand: x-Toeplitz band of each filter row, split into pieces
-    u16x8 B[C::NCH][PC::NBI];
-    {
-        const int j = lane % M::NT, g = lane / M::NT;
-        const int c = j / C::NX, xo = j % C::NX;
-#pragma unroll
-        for (int q = 0; q < C::NCH; ++q) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int b = C::SHAPE == 16 ? q * 4 + g : q;
-                const int ax = C::SHAPE == 16 ? e : 8 * g + e;
-                const int aa = ax - xo;
-                float wv = 0.f;
-                if (c < K && b < K && aa >= 0 && aa < K) wv = w[(c * K + b) * K + aa];
-                uint16_t p[3];
-                split_weight<PM>(wv, a.wscale, p);
-#pragma unroll
-                for (int bi = 0; bi < PC::NBI; ++bi) B[q][bi][e] = p[bi];
-            }
-        }
-    }
-
-    // ---- staging of the input plane: PITCH x HY cells from (x0 - r, y0 - r)
-    uint32_t goff[C::NE];
-    int32_t loff[C::NE];
-#pragma unroll
-    for (int i = 0; i < C::NE; ++i) {
-        int e = t + i * kNT;
-        if (e >= C::PITCH * C::HY) e = C::PITCH * C::HY - 1;
-        const int hy = e / C::PITCH, hx = e - hy * C::PITCH;
-        const int gx = addr_map((int64_t)x0 - R + hx, a.X, a.mode);
-        const int gy = addr_map((int64_t)y0 - R + hy, a.Y, a.mode);
-        // cells past the volume edge that only feed zero weights still read a
-        // finite value: clamp/wrap/mirror fetch them, border reads zero
-        goff[i] = (gx < 0 || gy < 0)
-                      ? kOutside
-                      : ((uint32_t)gy * (uint32_t)a.X + (uint32_t)gx) * (uint32_t)sizeof(T);
-        loff[i] = e;
-    }
-    // gather only issues the loads; the cells are split into their pieces
-    // when they are staged (put), after the plane's products, so the loads
-    // stay in flight while the matrix cores work
-    T raw[C::NE];
-    auto gather = [&](int zi) {
-        const int gz = addr_map(zi, a.Z, a.mode);
-        const char* base = reinterpret_cast<const char*>(src) +
-                           (gz < 0 ? 0 : (int64_t)gz * plane_bytes);
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<char*>(base), (short)0, gz < 0 ? 0 : plane_bytes, (int)kRsrcWord3);
-#pragma unroll
-        for (int i = 0; i < C::NE; ++i) raw[i] = buf_load<T>(rs, goff[i]);
-    };
-    auto put = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < C::NE; ++i) {
-            uint16_t p[3];
-            split_voxel<PM>(raw[i], p);
-#pragma unroll
-            for (int ps = 0; ps < PC::PS; ++ps) lds[buf][ps][loff[i]] = p[ps];
-        }
-    };
-
-    // ---- output block of the wave: its finished columns form an 8 (x) by
-    // BY = SY * MT (32 or 64) (y) block; lanes holding a finished column write
-    // it to the wave's LDS block (y fastest), then each lane reads its share of
-    // one row (8 cells, or 4 of a 32-row block) and stores it
-    constexpr int BX = C::WS * C::NX, BY = C::SY * M::MT;
-    static_assert(BX == 8 && (BY == 64 || BY == 32 || BY == 16), "8 x 64, 32 or 16 blocks");
-    // lane l stores CPL cells of row l % BY (for 32 rows, two lanes per row)
-    constexpr int CPL = BX * BY / 64;
     const int jcol = lane % M::NT, gq = lane / M::NT;
-    const int xo = jcol - (K - 1) * C::NX;  // finished column group k-1
-    const bool fin = xo >= 0 && xo < C::NX;
-    float* const blk = epi + wave * BX * BY;
+
+    // ---- B operand: x-Toeplitz band of each filter row, split into pieces;
+    // b: filter row, ax0: the first of its 8 input columns
+    auto weights = [&](int c, int xo, int b, int ax0, u16x8 (&v)[PC::NBI]) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int aa = ax0 + e - xo;
+            float wv = 0.f;
+            if (c < K && b < K && aa >= 0 && aa < K) wv = w[(c * K + b) * K + aa];
+            uint16_t p[3];
+            split_weight<PM>(wv, a.wscale, p);
+#pragma unroll
+            for (int bi = 0; bi < PC::NBI; ++bi) v[bi][e] = p[bi];
+        }
+    };
+    u16x8 B[TURN ? 1 : C::NCH][PC::NBI];  // 16x16 tiles: all of it, in registers
+    // 32x32 tiles: this lane's row of the table, moved on by a filter plane
+    // (NX rows) with each input plane: group s takes filter plane
+    // c = (p - s) mod k at input plane p of the slab
+    int boff = 0, blast = 0, bfirst = 0;
+    if constexpr (TURN) {
+        for (int i = t; i < C::NCH * 2 * C::BROWS; i += kNT) {
+            const int row = i % C::BROWS, g = (i / C::BROWS) % 2, q = i / (2 * C::BROWS);
+            u16x8 v[PC::NBI];
+            weights(row / NX, row % NX, q, 8 * g, v);
+#pragma unroll
+            for (int bi = 0; bi < PC::NBI; ++bi)
+                *reinterpret_cast<u16x8*>(&tab[(((q * PC::NBI + bi) * 2 + g) * C::BROWS + row) * 8]) =
+                    v[bi];
+        }
+        const int s = jcol / NX, xo = jcol % NX;
+        bfirst = (gq * C::BROWS + (s < K ? xo : C::BROWS - 1)) * 8;
+        blast = bfirst + (s < K ? (K - 1) * NX * 8 : 0);
+        boff = bfirst + (s < K ? (K - s) % K * NX * 8 : 0);
+    } else {
+#pragma unroll
+        for (int q = 0; q < C::NCH; ++q) weights(jcol / NX, jcol % NX, q * 4 + gq, 0, B[q]);
+    }
+
+    // ---- staging of the input plane: COLS x HY cells from (x0 - r, y0 - r);
+    // staged columns past X + r meet zero weights: they hold zeros
+    PlaneStage<T, R, C::HY, C::COLS, kNT, C> in;
+    in.init(a, x0, y0, t);
+    if (in.face) {
+        for (int e = t; e < 2 * PC::PS * C::PLANE / 8; e += kNT)
+            reinterpret_cast<u32x4*>(lds_base)[e] = u32x4{0u, 0u, 0u, 0u};
+        __syncthreads();
+    }
+    auto put = [&](int buf) __attribute__((always_inline)) {
+        in.put([&](const T (&v)[4], int e, bool on) __attribute__((always_inline)) {
+            stage_quad<PM>(lds[buf], v, e, on);
+        });
+    };
+
+    // ---- output block of the wave: its finished columns form a WX (x) by BY
+    // (y) block; lanes holding a finished column write it to the wave's LDS
+    // block (y fastest), then each lane reads CPL cells of one row and stores
+    // them
+    constexpr int BY = C::BY, CPL = C::CPL;
+    float* const blk = epi + wave * C::WX * BY;
     const int lrow = lane % BY, lpart = lane / BY;
-    const int xw = x0 + BX * wave + CPL * lpart, yl = y0 + lrow;
+    const int xw = x0 + C::WX * wave + CPL * lpart, yl = y0 + lrow;
     // rows past the volume's last row fall beyond the plane: dropped
     const uint32_t ooff =
         yl < a.ry1 ? ((uint32_t)yl * (uint32_t)a.X + (uint32_t)xw) * (uint32_t)sizeof(T) : kOutside;
-    const bool vec_row = a.vec_ok && xw + CPL <= a.rx1;
+    const bool vec_row = xw + CPL <= a.rx1;  // (buffer stores take any cell alignment)
 
     acc_t acc[C::MTW];
 #pragma unroll
@@ -264,33 +256,48 @@ __device__ void mfma_tile(const VolDesc& a, const float* __restrict__ w, int til
 
     // lane's A-operand coordinates inside an M tile
     const int ai = lane % M::MT, ag = lane / M::MT;
-    const int acol = C::NX * C::WS * wave + (C::SHAPE == 16 ? 0 : 8 * ag);
+    const int acol = C::WX * wave + (C::SHAPE == 16 ? 0 : 8 * ag);
 
+    // Before plane zi's products plane zi is in LDS and the loads of plane
+    // zi + 1 are in flight; it is staged after the products, and the loads of
+    // plane zi + 2 take its registers at once (a whole step to arrive).
     const int zi_beg = zb - R, zi_end = ze + R;
-    gather(zi_beg);
+    in.gather(a, zi_beg);
     put(0);
+    in.gather(a, min(zi_beg + 1, zi_end - 1));
     __syncthreads();
 
+    int done = TURN ? 1 : K - 1;  // column group that the next plane finishes
     for (int zi = zi_beg; zi < zi_end; ++zi) {
         const int cur = (zi - zi_beg) & 1;
-        gather(min(zi + 1, zi_end - 1));
 
         // (row block, K chunk) groups, software pipelined where C::PIPE: the
-        // LDS segments of group g + 1 are read while group g's products issue
+        // LDS segments (and weights) of group g + 1 are read while group g's
+        // products issue
         constexpr int NG = C::SY * C::NCH;
-        u32x4 seg[2][PC::PS][C::NRD];
-        auto load_seg = [&](int g, u32x4 (&sg)[PC::PS][C::NRD]) {
+        uint32_t seg[2][PC::PS][C::SEGD];
+        u16x8 Bt[2][PC::NBI];
+        auto load_seg = [&](int g, int h2) {
             const int yb = g / C::NCH, q = g % C::NCH;
             int b = C::SHAPE == 16 ? q * 4 + ag : q;
             if (b > K - 1) b = K - 1;  // zero weights there; keep A finite
-            const int row = yb * M::MT + ai + b;
+            const int off = C::at(yb * M::MT + ai + b, acol);
+            typedef uint32_t vrd __attribute__((ext_vector_type(C::RD)));
             // one segment per piece holds the windows of the wave's strips
 #pragma unroll
             for (int ps = 0; ps < PC::PS; ++ps)
 #pragma unroll
-                for (int h = 0; h < C::NRD; ++h)
-                    sg[ps][h] = *reinterpret_cast<const u32x4*>(
-                        &lds[cur][ps][row * C::PITCH + acol + 8 * h]);
+                for (int h = 0; h < C::SEGD / C::RD; ++h) {
+                    const vrd v = *reinterpret_cast<const vrd*>(&lds[cur][ps][off + 2 * C::RD * h]);
+#pragma unroll
+                    for (int d = 0; d < C::RD; ++d) seg[h2][ps][C::RD * h + d] = v[d];
+                }
+            if constexpr (TURN) {
+#pragma unroll
+                for (int bi = 0; bi < PC::NBI; ++bi)
+                    Bt[h2][bi] = *reinterpret_cast<const u16x8*>(
+                        &tab[boff + (q * PC::NBI + bi) * 2 * C::BROWS * 8]);
+            }
         };
         constexpr bool PIPE = C::PIPE;
         // the products at raised wave priority, higher with each third of
@@ -300,49 +307,59 @@ __device__ void mfma_tile(const VolDesc& a, const float* __restrict__ w, int til
         // and end together: 1024^3 uint16 11^3 16.4 ms, rising 15.25 ms, the
         // matrix cores 70 -> 80 % busy)
         __builtin_amdgcn_s_setprio(1);
-        load_seg(0, seg[0]);
+        load_seg(0, 0);
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
             if (g == (NG + 2) / 3) __builtin_amdgcn_s_setprio(2);
             if (g == (2 * NG + 2) / 3) __builtin_amdgcn_s_setprio(3);
             if constexpr (PIPE) {
-                if (g + 1 < NG) load_seg(g + 1, seg[(g + 1) & 1]);
+                if (g + 1 < NG) load_seg(g + 1, (g + 1) & 1);
                 // keep those reads ahead of this group's products
                 __builtin_amdgcn_sched_barrier(0);
             } else {
-                if (g > 0) load_seg(g, seg[g & 1]);
+                if (g > 0) load_seg(g, g & 1);
             }
             const int yb = g / C::NCH, q = g % C::NCH;
-            // strip s's window: dwords s .. s+3 of the segment
+            // strip s's window: the 8 cells from column NX s of the segment on
             u32x4 A[C::WS][PC::PS];
 #pragma unroll
             for (int st = 0; st < C::WS; ++st)
 #pragma unroll
                 for (int ps = 0; ps < PC::PS; ++ps)
 #pragma unroll
-                    for (int d = 0; d < 4; ++d)
-                        A[st][ps][d] = seg[g & 1][ps][(st + d) / 4][(st + d) % 4];
+                    for (int d = 0; d < 4; ++d) {
+                        const uint32_t(&sg)[C::SEGD] = seg[g & 1][ps];
+                        const int d0 = NX * st / 2 + d;
+                        A[st][ps][d] = NX * st % 2
+                                           ? __builtin_amdgcn_alignbit(sg[d0 + 1], sg[d0], 16)
+                                           : sg[d0];
+                    }
+            const u16x8(&Bq)[PC::NBI] = TURN ? Bt[g & 1] : B[TURN ? 0 : q];
             // products outer, strips inner: consecutive MFMAs are independent
 #pragma unroll
             for (int pr = 0; pr < PC::NPROD; ++pr)
 #pragma unroll
                 for (int st = 0; st < C::WS; ++st)
                     acc[yb * C::WS + st] = mfma<C::SHAPE, PC::F16>(
-                        A[st][PC::prod[pr][0]], B[q][PC::prod[pr][1]], acc[yb * C::WS + st]);
+                        A[st][PC::prod[pr][0]], Bq[PC::prod[pr][1]], acc[yb * C::WS + st]);
         }
+        if constexpr (TURN) boff = boff == blast ? bfirst : boff + NX * 8;
         // the next plane's cells are split and staged after the products
         __builtin_amdgcn_s_setprio(0);
         __builtin_amdgcn_sched_barrier(0);
         put(cur ^ 1);
+        in.gather(a, min(zi + 2, zi_end - 1));
 
-        // ---- column group k-1 holds output plane zi - r
+        // ---- column group `done` holds output plane zi - r
         const int zo = zi - R;
+        const int xo = jcol - done * NX;
+        const bool fin = xo >= 0 && xo < NX;
         if (zo >= zb) {
             if (fin) {
 #pragma unroll
                 for (int m = 0; m < C::MTW; ++m) {
                     const int yb = m / C::WS, st = m % C::WS;
-                    float* col = blk + (st * C::NX + xo) * BY + yb * M::MT + 4 * gq;
+                    float* col = blk + (st * NX + xo) * BY + yb * M::MT + 4 * gq;
 #pragma unroll
                     for (int qd = 0; qd < M::NACC / 4; ++qd)
                         *reinterpret_cast<f32x4*>(col + 8 * qd) =
@@ -354,7 +371,7 @@ __device__ void mfma_tile(const VolDesc& a, const float* __restrict__ w, int til
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             float v[CPL];
 #pragma unroll
-            for (int xl = 0; xl < CPL; ++xl) v[xl] = blk[(CPL * lpart + xl) * BY + lrow];
+            for (int x = 0; x < CPL; ++x) v[x] = blk[(CPL * lpart + x) * BY + lrow];
             const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
                 static_cast<char*>(a.dst) + (int64_t)zo * plane_bytes, (short)0, plane_bytes,
                 (int)kRsrcWord3);
@@ -362,10 +379,18 @@ __device__ void mfma_tile(const VolDesc& a, const float* __restrict__ w, int til
             asm volatile("" ::: "memory");
         }
         // ---- advance the ring
+        if constexpr (TURN) {
 #pragma unroll
-        for (int m = 0; m < C::MTW; ++m)
+            for (int m = 0; m < C::MTW; ++m)
 #pragma unroll
-            for (int r = 0; r < M::NACC; ++r) acc[m][r] = shift_cols<C::SHAPE, C::NX>(acc[m][r], lane);
+                for (int r = 0; r < M::NACC; ++r) acc[m][r] = fin ? 0.f : acc[m][r];
+            done = done + 1 == K ? 0 : done + 1;
+        } else {
+#pragma unroll
+            for (int m = 0; m < C::MTW; ++m)
+#pragma unroll
+                for (int r = 0; r < M::NACC; ++r) acc[m][r] = shift_cols<NX>(acc[m][r]);
+        }
         __syncthreads();
     }
 }
@@ -373,11 +398,14 @@ __device__ void mfma_tile(const VolDesc& a, const float* __restrict__ w, int til
 template <class C>
 constexpr int lds_elems()
 {
-    return 2 * C::PC::PS * C::HY * C::PITCH;
+    return 2 * C::PC::PS * C::PLANE;
 }
-// output transposition blocks: 4 waves x 8 x 64 floats (the 32-row blocks of
-// 16x16 tiles use half)
-constexpr int kEpiFloats = 4 * 8 * 64;
+// output transposition blocks of the 4 waves
+template <class C>
+constexpr int epi_floats()
+{
+    return 4 * C::WX * C::BY;
+}
 
 template <class C>
 __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(C::WAVES)))
@@ -386,10 +414,11 @@ void filter_mfma_kernel(VolDesc a,
                                                              uint32_t nblocks)
 {
     __shared__ __align__(16) uint16_t lds[lds_elems<C>()];
-    __shared__ __align__(16) float epi[kEpiFloats];
+    __shared__ __align__(16) float epi[epi_floats<C>()];
+    __shared__ __align__(16) uint16_t tab[C::TABLE];
     const uint32_t lid = xcd_remap(blockIdx.x, nblocks);
     const uint32_t ntiles = (uint32_t)a.tiles_x * (uint32_t)a.tiles_y;
-    mfma_tile<C>(a, w, (int)(lid % ntiles), (int)(lid / ntiles), lds, epi);
+    mfma_tile<C>(a, w, (int)(lid % ntiles), (int)(lid / ntiles), lds, epi, tab);
 }
 
 // Persistent workgroups over a queue of (volume, tile-slab) items; the last
@@ -399,7 +428,8 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(C::BWAVES))
 void filter_mfma_batched_kernel(BatchArgs b)
 {
     __shared__ __align__(16) uint16_t lds[lds_elems<C>()];
-    __shared__ __align__(16) float epi[kEpiFloats];
+    __shared__ __align__(16) float epi[epi_floats<C>()];
+    __shared__ __align__(16) uint16_t tab[C::TABLE];
     __shared__ uint32_t s_item;
     for (;;) {
         if (threadIdx.x == 0) s_item = atomicAdd(&b.counters[0], 1u);
@@ -413,7 +443,7 @@ void filter_mfma_batched_kernel(BatchArgs b)
         const VolDesc a = uniform_load(&b.vols[wi.vol]);
         const uint32_t ntiles = (uint32_t)a.tiles_x * (uint32_t)a.tiles_y;
         mfma_tile<C>(a, b.wpool + a.woff, (int)(wi.lid % ntiles), (int)(wi.lid / ntiles), lds,
-                     epi);
+                     epi, tab);
     }
     if (threadIdx.x == 0) {
         __threadfence();
@@ -450,9 +480,14 @@ hipError_t launch_cfg(const FilterJob& j, hipStream_t s)
     const int RX = j.roi[3] - j.roi[0], RY = j.roi[4] - j.roi[1], RZ = j.roi[5] - j.roi[2];
     const int64_t ntiles = (int64_t)((RX + g.tx - 1) / g.tx) * ((RY + g.ty - 1) / g.ty);
     const void* fn = (const void*)&filter_mfma_kernel<C>;
+    // Slots of the plan: the workgroups that fill the device once.  32x32 tiles
+    // keep the matrix cores busy with two workgroups per CU; planned for the
+    // three or four that fit, a small volume gets thinner slabs with more halo
+    // planes for nothing (150x141x133 uint16 11^3: 157 us, for two 136 us).
+    int slots = resident_wgs(fn);
+    if (C::SHAPE == 32) slots = std::min(slots, 2 * device_cus());
     // (deeper slabs measured slower for the 16x16 tiles, faster for 32x32)
-    const int tz = plan_tz(ntiles, RZ, j.k, 1, C::SHAPE == 16 ? 128 : 512,
-                           resident_wgs(fn), 1);
+    const int tz = plan_tz(ntiles, RZ, j.k, 1, C::SHAPE == 16 ? 128 : 512, slots, 1);
     const VolDesc a = make_desc(j, tz, g);
     const int64_t nb = ntiles * ((RZ + tz - 1) / tz);
     if (nb > 0x7fffffff) return hipErrorInvalidValue;

@@ -54,39 +54,6 @@ namespace vkt {
 namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-// Pieces of two adjacent cells, packed as the dword pairs they are staged as
-// (cell 0 in the low half): the pieces of split_voxel, converted two at a
-// time (one v_cvt_pk per pair; cells and their uint16 halves are exact in
-// fp16, so that the round-toward-zero packing changes nothing).
-template <int PM, typename T>
-__device__ inline void split_pair(T s0, T s1, uint32_t* pk)
-{
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    if constexpr (PM == kF32x3 || PM == kF32x6) {
-        const float x0 = (float)s0, x1 = (float)s1;
-        const uint32_t hu =
-            __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{x0, x1}), bf16x2));
-        const float r0 = x0 - __uint_as_float(hu << 16), r1 = x1 - __uint_as_float(hu & 0xffff0000u);
-        const uint32_t lu =
-            __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{r0, r1}), bf16x2));
-        pk[0] = hu;
-        pk[1] = lu;
-        if constexpr (PM == kF32x6) {
-            const float t0 = r0 - __uint_as_float(lu << 16), t1 = r1 - __uint_as_float(lu & 0xffff0000u);
-            pk[2] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{t0, t1}), bf16x2));
-        }
-    } else if constexpr (PM == kU16) {
-        const uint32_t v0 = s0, v1 = s1;
-        pk[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz((float)(v0 & 0xff00u),
-                                                                        (float)(v1 & 0xff00u)));
-        pk[1] = __builtin_bit_cast(uint32_t,
-                                   __builtin_amdgcn_cvt_pkrtz((float)(v0 & 255u), (float)(v1 & 255u)));
-    } else {
-        pk[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz((float)s0, (float)s1));
-    }
-}
-
 template <typename T, int K, int PM>
 struct RpCfg {
     using Tin = T;
@@ -106,7 +73,7 @@ struct RpCfg {
     // one pair apart, and 58 dwords put the 8-byte reads of 16 lanes into
     // different banks (56: 74 cycles for 40 bytes a lane instead of 24)
     static constexpr int PAIR = K == 5 ? 116 : 80;
-    static constexpr int at(int row, int col) { return (row >> 1) * PAIR + (row & 1) * PITCH + col; }
+    static __device__ constexpr int at(int row, int col) { return (row >> 1) * PAIR + (row & 1) * PITCH + col; }
     // dwords of a lane's segment: the windows of the wave's strips, read 8
     // bytes (24-byte wave offsets, k = 5) or 16 bytes at a time
     static constexpr int RD = WX % 8 == 0 ? 4 : 2;
@@ -115,7 +82,6 @@ struct RpCfg {
     static_assert(2 * 31 + 2 * (NCH - 1) + 1 < HY, "staged rows");
     static constexpr int PLANE = (HY / 2 * PAIR + 7) / 8 * 8;
     static_assert(HY % 2 == 0, "row pairs");
-    static constexpr int NQ = HY * PITCH / 4;       // staged quads
     // output rows in LDS (floats), read and written EV floats at a time
     static constexpr int EV = K == 5 ? 2 : 4;
     static constexpr int EPITCH = TX + EV;
@@ -126,29 +92,6 @@ struct RpCfg {
     static constexpr int LDS_BYTES = (2 * PC::PS * PLANE + TABLE) * 2 + 2 * TY * EPITCH * 4;
     static_assert(2 * LDS_BYTES <= 160 * 1024, "two workgroups per CU");
 };
-
-// Four consecutive cells at byte offset off (4-byte aligned): one 4-, 8- or
-// 16-byte buffer load.
-template <typename T>
-__device__ inline void buf_load4(__amdgpu_buffer_rsrc_t r, uint32_t off, T (&v)[4])
-{
-    if constexpr (sizeof(T) == 1) {
-        const uint32_t d = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = (T)(d >> (8 * j));
-    } else if constexpr (sizeof(T) == 2) {
-        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-        const u32x2 d = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0);
-        v[0] = (T)d[0];
-        v[1] = (T)(d[0] >> 16);
-        v[2] = (T)d[1];
-        v[3] = (T)(d[1] >> 16);
-    } else {
-        const u32x4 d = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = __uint_as_float(d[j]);
-    }
-}
 
 template <typename F, int... I>
 __device__ __attribute__((always_inline)) inline void static_for_impl(
@@ -230,111 +173,19 @@ __device__ void rp_tile(const VolDesc& a, const float* __restrict__ w, int tile,
         aoff = afirst + (sl < K ? (K - sl) % K * ASTEP : 0);
     }
 
-    // ---- staging of the input plane: PITCH x HY cells from (x0 - r, y0 - r),
-    // four adjacent cells (a quad) per thread and step, one 4-cell load each
-    // and no branch around it.  Quads that reach past an x face of the volume
-    // (at most three a row: one with columns left of cell 0, two with columns
-    // from X to X + r - 1) are staged apart, one per thread, by four cell
-    // loads through the address mode; only tiles at a face have any (a
-    // wave-uniform branch), and a quad past X + r stays zero, as it meets
-    // zero weights.  With the loads of a step fixed in number the compiler
-    // waits for exactly the plane it stages: four cell loads in a divergent
-    // branch for the face quads, as this kernel had them, put a memory latency
-    // into every plane step of a uint8 tile (302^3 5^3: 7000 cycles a step
-    // against 1536 of products) and made every second step wait for the loads
-    // it had just issued.
-    constexpr int NQ = C::NQ, QR = C::PITCH / 4;
-    constexpr int NE4 = (NQ + kNT - 1) / kNT;
-    static_assert(C::PITCH % 4 == 0 && R < 4, "quads inside rows, one left of cell 0");
-    static_assert(3 * C::HY <= kNT, "a face quad per thread");
-    const int xl = x0 - R;  // source column of staged column 0
-    const bool face = xl < 0 || xl + C::PITCH > a.X;
-    uint32_t goff[NE4];     // byte offset of the quad's 4-cell window
-    int qpos[NE4];          // its place in the staged plane
-    uint32_t inner = 0;     // bit i: quad i lies inside its row
-    const int32_t plane_cells = (int32_t)plane;
-#pragma unroll
-    for (int i = 0; i < NE4; ++i) {
-        const int e = min(t + i * kNT, NQ - 1);  // repeats the last quad (same values)
-        const int hy = e / QR, hx = 4 * (e % QR);
-        qpos[i] = C::at(hy, hx);
-        const int gy = addr_map((int64_t)y0 - R + hy, a.Y, a.mode);
-        const int xs = xl + hx;
-        // (a face quad's load stays inside the plane, of at least 4 cells; it
-        // is not staged; a row outside the volume under border mode reads 0)
-        const int32_t cell = min(max(gy, 0) * a.X + max(xs, 0), plane_cells - 4);
-        goff[i] = gy < 0 ? kOutside : (uint32_t)cell * (uint32_t)sizeof(T);
-        if (xs >= 0 && xs + 3 < a.X) inner |= 1u << i;
-    }
-    // this thread's face quad: byte offsets of its cells, its place in LDS
-    uint32_t foff[4];
-    int fe = -1;
-    if (face) {
-        const int q1 = (a.X - xl) / 4;  // the quad that holds column X
-        const int nl = xl < 0 ? 1 : 0;  // left quad 0, then right quads qr0 ...
-        const int qr0 = nl && q1 == 0 ? 1 : q1;
-        const int nr = (q1 < QR && qr0 == q1 ? 1 : 0) +
-                       (q1 + 1 < QR && 4 * (q1 + 1) < a.X + R - xl ? 1 : 0);
-        const int nf = nl + nr;
-        if (t < nf * C::HY) {
-            const int hy = t / nf, f = t - hy * nf;
-            const int qx = f < nl ? 0 : qr0 + f - nl;
-            const int gy = addr_map((int64_t)y0 - R + hy, a.Y, a.mode);
-            fe = C::at(hy, 4 * qx);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int gx = addr_map((int64_t)xl + 4 * qx + j, a.X, a.mode);
-                foff[j] = (gx < 0 || gy < 0)
-                              ? kOutside
-                              : ((uint32_t)gy * (uint32_t)a.X + (uint32_t)gx) * (uint32_t)sizeof(T);
-            }
-        }
+    // ---- staging of the input plane: PITCH x HY cells from (x0 - r, y0 - r);
+    // staged columns past X + r meet zero weights: they hold zeros
+    PlaneStage<T, R, C::HY, C::PITCH, kNT, C> in;
+    in.init(a, x0, y0, t);
+    if (in.face) {
         for (int e = t; e < 2 * PC::PS * PLANE / 8; e += kNT)
             reinterpret_cast<u32x4*>(lds_base)[e] = u32x4{0u, 0u, 0u, 0u};
         __syncthreads();
     }
-    // cells of the plane in flight (face cells in whole registers, so that no
-    // load has to be waited for to pack them)
-    using Tf = typename std::conditional<std::is_same<T, float>::value, float, uint32_t>::type;
-    T raw[NE4][4];
-    Tf fraw[4];
-    auto gather = [&](int zi) {
-        const int gz = addr_map(zi, a.Z, a.mode);
-        const char* base = reinterpret_cast<const char*>(a.src) +
-                           (gz < 0 ? 0 : (int64_t)gz * plane_bytes);
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<char*>(base), (short)0, gz < 0 ? 0 : plane_bytes, (int)kRsrcWord3);
-#pragma unroll
-        for (int i = 0; i < NE4; ++i) buf_load4<T>(rs, goff[i], raw[i]);
-        if (face && fe >= 0) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) fraw[j] = (Tf)buf_load<T>(rs, foff[j]);
-        }
-    };
-    auto put = [&](int buf) {
-        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-        auto stage = [&](const T (&v)[4], int e, bool on) {  // e: place of the quad's first cell
-            uint32_t p01[3], p23[3];
-            split_pair<PM>(v[0], v[1], p01);
-            split_pair<PM>(v[2], v[3], p23);
-            if (on) {
-#pragma unroll
-                for (int ps = 0; ps < PC::PS; ++ps)
-                    *reinterpret_cast<u32x2*>(&lds[buf][ps][e]) = u32x2{p01[ps], p23[ps]};
-            }
-        };
-        if (!face) {
-#pragma unroll
-            for (int i = 0; i < NE4; ++i) stage(raw[i], qpos[i], true);
-        } else {
-#pragma unroll
-            for (int i = 0; i < NE4; ++i)
-                stage(raw[i], qpos[i], (inner >> i) & 1u);
-            if (fe >= 0) {
-                const T v[4] = {(T)fraw[0], (T)fraw[1], (T)fraw[2], (T)fraw[3]};
-                stage(v, fe, true);
-            }
-        }
+    auto put = [&](int buf) __attribute__((always_inline)) {
+        in.put([&](const T (&v)[4], int e, bool on) __attribute__((always_inline)) {
+            stage_quad<PM>(lds[buf], v, e, on);
+        });
     };
 
     // ---- output: lane l holds row 2 (l % 32) + l / 32 of the tile at the
@@ -361,9 +212,9 @@ __device__ void rp_tile(const VolDesc& a, const float* __restrict__ w, int tile,
     const int bcol = C::WX * wave, boff = C::at(brow, bcol);
 
     const int zi_beg = zb - R, zi_end = ze + R;
-    gather(zi_beg);
+    in.gather(a, zi_beg);
     put(0);
-    gather(min(zi_beg + 1, zi_end - 1));
+    in.gather(a, min(zi_beg + 1, zi_end - 1));
     __syncthreads();
 
     // One input plane zi = zi_beg + p, U = p mod k; LDS buffer cur holds it,
@@ -442,7 +293,7 @@ __device__ void rp_tile(const VolDesc& a, const float* __restrict__ w, int tile,
         __builtin_amdgcn_s_setprio(0);
         __builtin_amdgcn_sched_barrier(0);
         put(cur ^ 1);
-        gather(min(zi + 2, zi_end - 1));
+        in.gather(a, min(zi + 2, zi_end - 1));
 
         // ---- ring slot U + 1 holds output plane zi - r; it restarts at zero
         constexpr int done = (U + 1) % K;

@@ -260,6 +260,8 @@ VolDesc make_desc(const FilterJob& j, int tz, ClassGeom g);
 // Workgroups of 256 threads of `func` resident on the whole current device
 // at once (occupancy x compute units), cached per (kernel, device).
 int resident_wgs(const void* func);
+// Compute units of the current device.
+int device_cus();
 // Z-slab depth of a single-volume launch of ntiles tiles per plane: the
 // depth in [tz_min, tz_max] (tz = 1 mod `mod` when mod > 1) that minimises
 // rounds x (tz + k - 1), where a round is one wave of `slots` resident

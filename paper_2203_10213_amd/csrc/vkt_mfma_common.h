@@ -13,7 +13,7 @@
 // largest |w| lands in [2^14, 2^15); the result is scaled back by 2^-s.
 #pragma once
 
-#include "vkt_internal.h"
+#include "vkt_stage.h"
 
 #include <type_traits>
 
@@ -28,8 +28,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kNT = 256;                     // threads per workgroup (4 waves)
-constexpr uint32_t kRsrcWord3 = 0x00020000u; // gfx9-family raw buffer
-constexpr uint32_t kOutside = 0x80000000u;   // byte offset that is dropped / reads 0
 
 // Operand pieces and the products kept.
 enum PieceMode { kU8 = 0, kU16 = 1, kF32x3 = 2, kF32x6 = 3 };
@@ -61,18 +59,6 @@ __device__ inline uint32_t xcd_remap(uint32_t b, uint32_t n)
     return xcd < rem ? xcd * (q + 1) + idx : rem * (q + 1) + (xcd - rem) * q + idx;
 }
 
-template <typename T>
-__device__ inline T buf_load(__amdgpu_buffer_rsrc_t r, uint32_t off)
-{
-    if constexpr (sizeof(T) == 1) {
-        return (T)__builtin_amdgcn_raw_buffer_load_b8(r, (int)off, 0, 0);
-    } else if constexpr (sizeof(T) == 2) {
-        return (T)__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, 0);
-    } else {
-        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
-    }
-}
-
 __device__ inline uint16_t f16_bits(float x) { return __builtin_bit_cast(uint16_t, (_Float16)x); }
 __device__ inline float f16_val(uint16_t h) { return (float)__builtin_bit_cast(_Float16, h); }
 __device__ inline uint16_t bf16_bits(float x) { return __builtin_bit_cast(uint16_t, (__bf16)x); }
@@ -94,6 +80,56 @@ __device__ inline void split_voxel(T s, uint16_t* p)
         const float r1 = x - bf16_val(p[0]);
         p[1] = bf16_bits(r1);
         if constexpr (PM == kF32x6) p[2] = bf16_bits(r1 - bf16_val(p[1]));
+    }
+}
+
+// Pieces of two adjacent cells, packed as the dword pairs they are staged as
+// (cell 0 in the low half): the pieces of split_voxel, converted two at a
+// time (one v_cvt_pk per pair; cells and their uint16 halves are exact in
+// fp16, so that the round-toward-zero packing changes nothing).
+template <int PM, typename T>
+__device__ inline void split_pair(T s0, T s1, uint32_t* pk)
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    if constexpr (PM == kF32x3 || PM == kF32x6) {
+        const float x0 = (float)s0, x1 = (float)s1;
+        const uint32_t hu =
+            __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{x0, x1}), bf16x2));
+        const float r0 = x0 - __uint_as_float(hu << 16), r1 = x1 - __uint_as_float(hu & 0xffff0000u);
+        const uint32_t lu =
+            __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{r0, r1}), bf16x2));
+        pk[0] = hu;
+        pk[1] = lu;
+        if constexpr (PM == kF32x6) {
+            const float t0 = r0 - __uint_as_float(lu << 16), t1 = r1 - __uint_as_float(lu & 0xffff0000u);
+            pk[2] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{t0, t1}), bf16x2));
+        }
+    } else if constexpr (PM == kU16) {
+        const uint32_t v0 = s0, v1 = s1;
+        pk[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz((float)(v0 & 0xff00u),
+                                                                        (float)(v1 & 0xff00u)));
+        pk[1] = __builtin_bit_cast(uint32_t,
+                                   __builtin_amdgcn_cvt_pkrtz((float)(v0 & 255u), (float)(v1 & 255u)));
+    } else {
+        pk[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz((float)s0, (float)s1));
+    }
+}
+
+// Stages four cells' pieces at plane[piece][e], one 8-byte write a piece
+// (none if !on).
+template <int PM, typename T, int PLANE>
+__device__ __attribute__((always_inline)) inline void stage_quad(uint16_t (*plane)[PLANE], const T (&v)[4],
+                                                                 int e, bool on)
+{
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    uint32_t p01[3], p23[3];
+    split_pair<PM>(v[0], v[1], p01);
+    split_pair<PM>(v[2], v[3], p23);
+    if (on) {
+#pragma unroll
+        for (int ps = 0; ps < Pieces<PM>::PS; ++ps)
+            *reinterpret_cast<u32x2*>(&plane[ps][e]) = u32x2{p01[ps], p23[ps]};
     }
 }
 
@@ -155,18 +191,25 @@ __device__ inline void store_row(__amdgpu_buffer_rsrc_t r, uint32_t off, const f
     }
     if (vec) {
         constexpr int CPD = 4 / sizeof(T);  // cells per dword
-        if constexpr (N < CPD) {
-            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(u[0] | (u[1] << 8)), r, (int)off, 0, 0);
-        } else {
-            uint32_t d[N / CPD];
+        constexpr int W = N / CPD, REST = N % CPD;
+        if constexpr (W > 0) {
+            uint32_t d[W];
 #pragma unroll
-            for (int i = 0; i < N / CPD; ++i) {
+            for (int i = 0; i < W; ++i) {
                 d[i] = u[CPD * i];
 #pragma unroll
                 for (int c = 1; c < CPD; ++c) d[i] |= u[CPD * i + c] << (8 * sizeof(T) * c);
             }
-            store_dwords<N / CPD>(r, off, d);
+            store_dwords<W>(r, off, d);
         }
+        const int o = (int)off + 4 * W;
+        if constexpr (sizeof(T) == 2 && REST == 1)
+            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)u[CPD * W], r, o, 0, 0);
+        if constexpr (sizeof(T) == 1 && REST >= 2)
+            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(u[CPD * W] | (u[CPD * W + 1] << 8)), r, o,
+                                                  0, 0);
+        if constexpr (sizeof(T) == 1 && REST % 2 == 1)
+            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)u[N - 1], r, o + (REST & 2), 0, 0);
     } else {
 #pragma unroll
         for (int i = 0; i < N; ++i) {
