@@ -17,21 +17,70 @@
 // Flip: dst(x) = src(n - 1 - x) along one axis; in place (dst == src) the
 // first half along the axis swaps with the mirrored half.
 //
-// Both are HBM-bound streams.  Launch shape: threadIdx.x runs along a row
-// (cells, or 16-byte chunks on the vector paths), threadIdx.y over rows, the
-// grid over row groups with a row-stride loop; blocks are 256 threads whose
-// x extent is the power of two covering a row (at most 256), so short rows
-// still fill whole wavefronts.  The vector paths (16-byte loads and stores)
-// run when rows are whole 16-byte chunks and both buffers are 16-byte
-// aligned; otherwise one thread per cell.
+// All are HBM-bound streams at best.  The halving and flip kernels move 16
+// bytes per thread at any cell alignment (rows that are not whole 16-byte
+// chunks end in a chunk moved back to the row's end); items are numbered
+// through rows and planes and taken apart with multiplications.
 #include "vkt_internal.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace vkt {
 namespace {
 
 constexpr int kNT = 256;
+
+// Items of the rows [y0, y0 + ny) x [z0, z0 + nz) of a volume, `items` per
+// row, numbered through; one thread each.
+struct RowBox {
+    int32_t y0, z0, ny;
+    uint32_t total;          // items in the box (below 2^31)
+    int32_t items;
+    UDiv per_row, per_plane;  // by items, by ny
+};
+
+__device__ inline uint32_t udiv(uint32_t n, UDiv d)
+{
+    const uint32_t t = __umulhi(d.m, n);
+    return (t + ((n - t) >> d.sh1)) >> d.sh2;
+}
+
+// This thread's item: false past the last one.
+__device__ inline bool row_item(const RowBox& b, int& c, int& y, int& z)
+{
+    const uint32_t i = blockIdx.x * (uint32_t)kNT + threadIdx.x;
+    if (i >= b.total) return false;
+    const uint32_t row = udiv(i, b.per_row), zr = udiv(row, b.per_plane);
+    c = (int)(i - row * (uint32_t)b.items);
+    y = b.y0 + (int)(row - zr * (uint32_t)b.ny);
+    z = b.z0 + (int)zr;
+    return true;
+}
+
+// launch(box, blocks) for boxes that cover Ys x Zs rows.
+template <typename F>
+hipError_t for_row_boxes(int Ys, int Zs, int items, F&& launch)
+{
+    RowBox b{};
+    b.items = items;
+    b.per_row = make_udiv((uint32_t)items);
+    const int64_t most = (((int64_t)1 << 31) - 1) / items;
+    const int ny = (int)std::min<int64_t>(Ys, std::max<int64_t>(1, most));
+    const int nz = ny < Ys ? 1 : (int)std::min<int64_t>(Zs, std::max<int64_t>(1, most / Ys));
+    for (int z0 = 0; z0 < Zs; z0 += std::min(nz, Zs - z0))
+        for (int y0 = 0; y0 < Ys; y0 += std::min(ny, Ys - y0)) {
+            b.y0 = y0;
+            b.z0 = z0;
+            b.ny = std::min(ny, Ys - y0);
+            b.per_plane = make_udiv((uint32_t)b.ny);
+            b.total = (uint32_t)((int64_t)items * b.ny * std::min(nz, Zs - z0));
+            launch(b, dim3((b.total + kNT - 1) / kNT));
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+    return hipSuccess;
+}
 
 struct RowGrid {
     dim3 grid, block;
@@ -90,20 +139,205 @@ __device__ inline void lin_axis(int i, int n, int m, int& i0, int& i1, float& f)
 
 __device__ inline float lerp(float a, float b, float t) { return a + t * (b - a); }
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-// 16-byte load that is read once (streamed past the caches' reuse sets).
-__device__ inline uint4 load_stream(const uint4* p)
+// 16 bytes at any cell alignment; loads are read once (streamed past the
+// caches' reuse sets).
+typedef uint32_t chunk16 __attribute__((ext_vector_type(4), aligned(1)));
+__device__ inline uint4 load_stream(const void* p)
 {
-    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+    const chunk16 v = __builtin_nontemporal_load(static_cast<const chunk16*>(p));
     return make_uint4(v.x, v.y, v.z, v.w);
 }
+__device__ inline void store16(void* p, uint4 v)
+{
+    *static_cast<chunk16*>(p) = chunk16{v.x, v.y, v.z, v.w};
+}
 
-// ---- general trilinear resampling: one destination cell per thread -------
+// ---- general trilinear resampling ------------------------------------------
+// A thread takes 4 adjacent destination cells of a row (the groups of all rows
+// numbered through, so that no lane idles) and marches through up to kZC
+// destination planes, fewer where the volume would not fill the device.  Per source plane it needs, a lane
+// loads the cell pairs (x0, x0 + 1) of its two source rows -- in the plane at
+// one uniform address and a 32-bit offset kept over the march -- interpolates
+// them along x and y, and keeps the result while further destination planes
+// lie between the same source planes.  The sums are those of one cell at a
+// time (x, then y, then z).  What bounded the one-cell-per-thread form (302^3
+// uint8 to 403^3: 401 us, 93 MB) were some 300 instructions a cell, most of
+// them the integer divisions of its three positions; here x and y positions
+// are worked out once per march and z positions once per workgroup (LDS), and
+// the same call takes 52 us at some 20 vector instructions a cell, which bound it
+// (the vector ALUs 66 % busy).
+constexpr int kZC = 32;   // destination planes per march at most
+constexpr int kXV = 4;    // adjacent destination cells per thread
+
+struct ZPos {
+    int z0, z1;
+    float f;
+    int pad;
+};
+
+// Two adjacent cells at byte offset off of a plane (any cell alignment).
 template <typename T>
+__device__ inline void load_pair(__amdgpu_buffer_rsrc_t r, uint32_t off, float& lo, float& hi)
+{
+    if constexpr (std::is_same<T, float>::value) {
+        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0);
+        lo = __uint_as_float(v[0]);
+        hi = __uint_as_float(v[1]);
+    } else if constexpr (std::is_same<T, uint16_t>::value) {
+        const uint32_t v = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0);
+        lo = (float)(v & 0xffffu);
+        hi = (float)(v >> 16);
+    } else {
+        const uint32_t v = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, 0);
+        lo = (float)(v & 0xffu);
+        hi = (float)(v >> 8);
+    }
+}
+
+// WIDE (uint8 cells, source at most twice the destination along x, planes of at
+// least 8 cells): a thread's four pairs lie in 8 adjacent cells, which one
+// load brings; v_perm picks the pairs (302^3 to 403^3: 52 us instead of 70).
+template <typename T, bool WIDE>
 __global__ __launch_bounds__(kNT) void resample_kernel(const T* __restrict__ src,
                                                        T* __restrict__ dst, int X, int Y, int Z,
-                                                       int Xo, int Yo, int Zo, int64_t nrows)
+                                                       int Xo, int Yo, int Zo, int zc,
+                                                       uint32_t groups, UDiv per_row)
+{
+    __shared__ ZPos zpos[kZC];
+    const int t = threadIdx.x;
+    const int zb = (int)blockIdx.y * zc, nz = min(zc, Zo - zb);
+    if (t < nz) {
+        ZPos p{};
+        lin_axis(zb + t, Z, Zo, p.z0, p.z1, p.f);
+        zpos[t] = p;
+    }
+    __syncthreads();
+    const uint32_t item = blockIdx.x * (uint32_t)kNT + (uint32_t)t;
+    const uint32_t row = udiv(item, per_row);
+    const int y = (int)row, x = (int)(item - row * groups) * kXV;
+    if (y >= Yo) return;
+    int y0, y1;
+    float fy;
+    lin_axis(y, Y, Yo, y0, y1, fy);
+    // pairs start at xb <= X - 2; a clamped position (x0 == x1) takes one of
+    // the pair's cells: float32 both times, integer cells, which cannot
+    // overflow, at the fraction 0 or 1 (the same value exactly)
+    uint32_t off[2][kXV];
+    float fx[kXV];
+    uint32_t low2 = 0, high2 = 0;  // bit j: both cells are the pair's first / second
+#pragma unroll
+    for (int j = 0; j < kXV; ++j) {
+        int x0, x1;
+        lin_axis(min(x + j, Xo - 1), X, Xo, x0, x1, fx[j]);
+        const int xb = min(x0, X - 2);
+        if constexpr (std::is_same<T, float>::value) {
+            if (x1 == xb) low2 |= 1u << j;
+            if (x0 != xb) high2 |= 1u << j;
+        } else {
+            if (x1 == xb) fx[j] = 0.f;
+            if (x0 != xb) fx[j] = 1.f;
+        }
+        off[0][j] = ((uint32_t)y0 * (uint32_t)X + (uint32_t)xb) * (uint32_t)sizeof(T);
+        off[1][j] = ((uint32_t)y1 * (uint32_t)X + (uint32_t)xb) * (uint32_t)sizeof(T);
+    }
+    uint32_t wide[2] = {};  // WIDE: the 8 cells' offset; off[][] then holds byte selectors
+    if constexpr (WIDE) {
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            wide[r] = min(off[r][0], (uint32_t)X * (uint32_t)Y - 8u);  // inside the plane
+#pragma unroll
+            for (int j = 0; j < kXV; ++j) {
+                const uint32_t d = off[r][j] - wide[r];
+                off[r][j] = d | (d + 1u) << 8 | 0x0c0c0000u;
+            }
+        }
+    }
+    const int64_t plane = (int64_t)X * Y, oplane = (int64_t)Xo * Yo;
+    // rows of one source plane interpolated along x, then y
+    auto at_plane = [&](int z, float (&v)[kXV]) {
+        const __amdgpu_buffer_rsrc_t p = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<T*>(src + z * plane), (short)0, (int)(uint32_t)(plane * (int64_t)sizeof(T)),
+            0x00020000);
+        float lo[2][kXV], hi[2][kXV];
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int j = 0; j < kXV; ++j)
+                if constexpr (!WIDE) load_pair<T>(p, off[r][j], lo[r][j], hi[r][j]);
+        if constexpr (WIDE) {
+            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+            u32x2 w[2];
+#pragma unroll
+            for (int r = 0; r < 2; ++r) w[r] = __builtin_amdgcn_raw_buffer_load_b64(p, (int)wide[r], 0, 0);
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int j = 0; j < kXV; ++j) {
+                    const uint32_t v = __builtin_amdgcn_perm(w[r][1], w[r][0], off[r][j]);
+                    lo[r][j] = (float)(v & 0xffu);
+                    hi[r][j] = (float)((v >> 8) & 0xffu);
+                }
+        }
+#pragma unroll
+        for (int j = 0; j < kXV; ++j) {
+            float a[2];
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const float c0 = (high2 >> j) & 1u ? hi[r][j] : lo[r][j];
+                const float c1 = (low2 >> j) & 1u ? lo[r][j] : hi[r][j];
+                a[r] = lerp(c0, c1, fx[j]);
+            }
+            v[j] = lerp(a[0], a[1], fy);
+        }
+    };
+    T* out = dst + zb * oplane + (int64_t)y * Xo + x;
+    const bool whole = x + kXV <= Xo;
+    int have0 = -1, have1 = -1;  // source planes whose values are at hand
+    float v0[kXV] = {}, v1[kXV] = {};
+    for (int i = 0; i < nz; ++i, out += oplane) {
+        const int z0 = __builtin_amdgcn_readfirstlane(zpos[i].z0);
+        const int z1 = __builtin_amdgcn_readfirstlane(zpos[i].z1);
+        const float fz = zpos[i].f;
+        if (z0 != have0) {
+            if (z0 == have1) {
+#pragma unroll
+                for (int j = 0; j < kXV; ++j) v0[j] = v1[j];
+            } else {
+                at_plane(z0, v0);
+            }
+            have0 = z0;
+        }
+        if (z1 != have1) {
+            if (z1 == z0) {
+#pragma unroll
+                for (int j = 0; j < kXV; ++j) v1[j] = v0[j];
+            } else {
+                at_plane(z1, v1);
+            }
+            have1 = z1;
+        }
+        T r[kXV];
+#pragma unroll
+        for (int j = 0; j < kXV; ++j) r[j] = from_f<T>(lerp(v0[j], v1[j], fz));
+        if (whole) {
+            typedef T vec __attribute__((ext_vector_type(kXV), aligned(sizeof(T))));
+            *reinterpret_cast<vec*>(out) = vec{r[0], r[1], r[2], r[3]};
+        } else {
+#pragma unroll
+            for (int j = 0; j < kXV; ++j)
+                if (x + j < Xo) out[j] = r[j];
+        }
+    }
+}
+
+// One destination cell per thread: sources one cell wide, planes of 4 GiB and
+// more, and grids beyond the launch limits of the kernel above.
+template <typename T>
+__global__ __launch_bounds__(kNT) void resample_cell_kernel(const T* __restrict__ src,
+                                                            T* __restrict__ dst, int X, int Y,
+                                                            int Z, int Xo, int Yo, int Zo,
+                                                            int64_t nrows)
 {
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
     if (x >= Xo) return;
@@ -129,7 +363,8 @@ __global__ __launch_bounds__(kNT) void resample_kernel(const T* __restrict__ src
     }
 }
 
-// ---- exact downscale by two: one destination cell per thread -------------
+// ---- exact downscale by two: one destination cell per thread (rows shorter
+// than 16 bytes) ---------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(kNT) void halve_kernel(const T* __restrict__ src,
                                                     T* __restrict__ dst, int X, int Y, int Xo,
@@ -218,61 +453,29 @@ __device__ inline void halve_chunk(const uint4 (&a)[4], const uint4 (&b)[4], uin
 }
 
 template <typename T>
-__global__ __launch_bounds__(kNT) void halve_vec_kernel(const uint4* __restrict__ src,
-                                                        uint4* __restrict__ dst, int cpr,
-                                                        int Yo, int64_t nrows)
+__global__ __launch_bounds__(kNT) void halve_vec_kernel(const T* __restrict__ src,
+                                                        T* __restrict__ dst, int Xo, int Yo,
+                                                        RowBox box)
 {
-    // cpr: 16-byte chunks per destination row; a source row has 2 cpr
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cpr) return;
-    const int64_t srow = 2 * (int64_t)cpr;        // chunks per source row
-    const int64_t splane = srow * 2 * Yo;         // chunks per source plane
-    for (int64_t r = (int64_t)blockIdx.y * blockDim.y + threadIdx.y; r < nrows;
-         r += (int64_t)gridDim.y * blockDim.y) {
-        const int y = (int)(r % Yo), z = (int)(r / Yo);
-        const uint4* s0 = src + (2 * z) * splane + (2 * y) * srow + 2 * c;
-        const uint4* rows[4] = {s0, s0 + srow, s0 + splane, s0 + splane + srow};
-        uint4 a[4], b[4];
+    constexpr int CPC = 16 / sizeof(T);
+    int c, y, z;
+    if (!row_item(box, c, y, z)) return;
+    const int x = min(c * CPC, Xo - CPC);  // the last chunk ends the row
+    const int64_t X = 2 * (int64_t)Xo, plane = X * 2 * Yo;
+    const T* s0 = src + (2 * (int64_t)z) * plane + (2 * (int64_t)y) * X + 2 * (int64_t)x;
+    const T* rows[4] = {s0, s0 + X, s0 + plane, s0 + plane + X};
+    uint4 a[4], b[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            a[i] = load_stream(rows[i]);
-            b[i] = load_stream(rows[i] + 1);
-        }
-        uint4 o;
-        halve_chunk<T>(a, b, o);
-        dst[r * cpr + c] = o;
+    for (int i = 0; i < 4; ++i) {
+        a[i] = load_stream(rows[i]);
+        b[i] = load_stream(rows[i] + CPC);
     }
+    uint4 o;
+    halve_chunk<T>(a, b, o);
+    store16(dst + ((int64_t)z * Yo + y) * Xo + x, o);
 }
 
 // ---- Flip ----------------------------------------------------------------
-// One cell per thread.  Out of place: every cell; in place: the cells with
-// coordinate < n / 2 along the axis swap with their mirror (the middle cell
-// of an odd axis stays).  Xs / Ys: cells per row / rows per plane iterated.
-template <typename T>
-__global__ __launch_bounds__(kNT) void flip_kernel(const T* src, T* dst, int X, int Y, int Z,
-                                                   int Xs, int Ys, int64_t nrows, int axis,
-                                                   int inplace)
-{
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    if (x >= Xs) return;
-    const int mx = axis == 0 ? X - 1 - x : x;
-    for (int64_t r = (int64_t)blockIdx.y * blockDim.y + threadIdx.y; r < nrows;
-         r += (int64_t)gridDim.y * blockDim.y) {
-        const int y = (int)(r % Ys), z = (int)(r / Ys);
-        const int my = axis == 1 ? Y - 1 - y : y;
-        const int mz = axis == 2 ? Z - 1 - z : z;
-        const int64_t o = ((int64_t)z * Y + y) * X + x;
-        const int64_t m = ((int64_t)mz * Y + my) * X + mx;
-        if (inplace) {
-            const T a = dst[o], b = dst[m];
-            dst[o] = b;
-            dst[m] = a;
-        } else {
-            dst[o] = src[m];
-        }
-    }
-}
-
 // The cells of a 16-byte chunk in reverse order.
 template <typename T>
 __device__ inline uint4 reverse_chunk(uint4 v)
@@ -288,38 +491,46 @@ __device__ inline uint4 reverse_chunk(uint4 v)
     }
 }
 
-// 16-byte chunks per thread; rows are cpr whole chunks.  Along x, chunk c
-// of a row comes from chunk cpr - 1 - c with its cells reversed; along y or
-// z whole chunks move between mirrored rows.  In place along x only the
-// first ceil(cpr / 2) chunks are visited (the middle chunk of an odd count
-// is reversed by itself); along y or z only the first half of the rows.
+// Rows of the box [y0, y0 + ny) x [z0, z0 + nz), `items` per row: nvec 16-byte
+// chunks, then single cells.  Out of place: every byte of a row; rows that are
+// no whole chunks end in a chunk moved back to the row's end (rewriting some of
+// its neighbour with the same values), rows shorter than a chunk go by cells.
+// In place, item i swaps with its mirror: along x the chunks and cells of the
+// first half (nvec chunks from either end, the cells between them), along y or
+// z the first half of the rows, whole chunks and the cells behind them.  At any
+// cell alignment: the one-cell-per-thread form that ragged rows took needed 76
+// us for 302^3 uint8 along x (55 MB), two 64-bit divisions a cell.
+struct FlipArgs {
+    int32_t X, Y, Z;
+    int32_t nvec;
+    int32_t axis;
+    int32_t inplace;
+};
+
 template <typename T>
-__global__ __launch_bounds__(kNT) void flip_vec_kernel(const uint4* src, uint4* dst, int cpr,
-                                                       int Y, int Z, int cs, int Ys,
-                                                       int64_t nrows, int axis, int inplace)
+__global__ __launch_bounds__(kNT) void flip_kernel(const T* src, T* dst, FlipArgs a, RowBox box)
 {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cs) return;
-    const int mc = axis == 0 ? cpr - 1 - c : c;
-    for (int64_t r = (int64_t)blockIdx.y * blockDim.y + threadIdx.y; r < nrows;
-         r += (int64_t)gridDim.y * blockDim.y) {
-        const int y = (int)(r % Ys), z = (int)(r / Ys);
-        const int my = axis == 1 ? Y - 1 - y : y;
-        const int mz = axis == 2 ? Z - 1 - z : z;
-        const int64_t o = ((int64_t)z * Y + y) * cpr + c;
-        const int64_t m = ((int64_t)mz * Y + my) * cpr + mc;
-        if (inplace) {
-            const uint4 a = dst[o], b = dst[m];
-            dst[o] = axis == 0 ? reverse_chunk<T>(b) : b;
-            dst[m] = axis == 0 ? reverse_chunk<T>(a) : a;
-        } else {
-            const uint4 b = load_stream(src + m);
-            dst[o] = axis == 0 ? reverse_chunk<T>(b) : b;
-        }
+    constexpr int CPC = 16 / sizeof(T);  // cells per chunk
+    int c, y, z;
+    if (!row_item(box, c, y, z)) return;
+    const int my = a.axis == 1 ? a.Y - 1 - y : y;
+    const int mz = a.axis == 2 ? a.Z - 1 - z : z;
+    const int64_t o = ((int64_t)z * a.Y + y) * a.X, m = ((int64_t)mz * a.Y + my) * a.X;
+    if (c < a.nvec) {
+        const int x = a.inplace ? c * CPC : min(c * CPC, a.X - CPC);
+        const int mx = a.axis == 0 ? a.X - CPC - x : x;
+        const uint4 b = load_stream(src + m + mx);
+        const uint4 w = a.inplace ? load_stream(src + o + x) : b;
+        store16(dst + o + x, a.axis == 0 ? reverse_chunk<T>(b) : b);
+        if (a.inplace) store16(dst + m + mx, a.axis == 0 ? reverse_chunk<T>(w) : w);
+    } else {
+        const int x = (a.inplace ? a.nvec * CPC : 0) + c - a.nvec;
+        const int mx = a.axis == 0 ? a.X - 1 - x : x;
+        const T b = src[m + mx], w = a.inplace ? src[o + x] : b;
+        dst[o + x] = b;
+        if (a.inplace) dst[m + mx] = w;
     }
 }
-
-bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 template <typename T>
 hipError_t resample_t(const void* src, void* dst, const int32_t in[3], const int32_t out[3],
@@ -327,21 +538,42 @@ hipError_t resample_t(const void* src, void* dst, const int32_t in[3], const int
 {
     const int64_t nrows = (int64_t)out[1] * out[2];
     const bool halve = in[0] == 2 * out[0] && in[1] == 2 * out[1] && in[2] == 2 * out[2];
-    if (halve && ((int64_t)out[0] * sizeof(T)) % 16 == 0 && aligned16(src) && aligned16(dst)) {
-        const int cpr = (int)((int64_t)out[0] * sizeof(T) / 16);
-        const RowGrid g = row_grid(cpr, nrows);
-        hipLaunchKernelGGL((halve_vec_kernel<T>), g.grid, g.block, 0, s,
-                           static_cast<const uint4*>(src), static_cast<uint4*>(dst), cpr, out[1],
-                           nrows);
+    constexpr int CPC = 16 / sizeof(T);
+    if (halve && out[0] >= CPC) {
+        return for_row_boxes(out[1], out[2], (int)(((int64_t)out[0] + CPC - 1) / CPC),
+                             [&](const RowBox& b, dim3 blocks) {
+                                 hipLaunchKernelGGL((halve_vec_kernel<T>), blocks, dim3(kNT), 0, s,
+                                                    static_cast<const T*>(src),
+                                                    static_cast<T*>(dst), out[0], out[1], b);
+                             });
     } else if (halve) {
         const RowGrid g = row_grid(out[0], nrows);
         hipLaunchKernelGGL((halve_kernel<T>), g.grid, g.block, 0, s, static_cast<const T*>(src),
                            static_cast<T*>(dst), in[0], in[1], out[0], out[1], nrows);
     } else {
-        const RowGrid g = row_grid(out[0], nrows);
-        hipLaunchKernelGGL((resample_kernel<T>), g.grid, g.block, 0, s,
-                           static_cast<const T*>(src), static_cast<T*>(dst), in[0], in[1], in[2],
-                           out[0], out[1], out[2], nrows);
+        const int64_t groups = ((int64_t)out[0] + kXV - 1) / kXV;
+        const int64_t gx = (groups * out[1] + kNT - 1) / kNT;
+        // marches as long as the device still gets 8 workgroups per CU
+        const int64_t zc =
+            std::min<int64_t>(kZC, std::max<int64_t>(1, gx * out[2] / (8 * device_cus())));
+        const int64_t gz = ((int64_t)out[2] + zc - 1) / zc;
+        if (in[0] >= 2 && (int64_t)in[0] * in[1] * (int64_t)sizeof(T) < ((int64_t)1 << 32) &&
+            gx * kNT <= INT32_MAX && gz <= 65535) {
+            auto* kernel = &resample_kernel<T, false>;
+            if constexpr (std::is_same<T, uint8_t>::value) {
+                if (in[0] <= 2 * (int64_t)out[0] && (int64_t)in[0] * in[1] >= 8)
+                    kernel = &resample_kernel<T, true>;
+            }
+            hipLaunchKernelGGL(kernel, dim3((unsigned)gx, (unsigned)gz), dim3(kNT), 0, s,
+                               static_cast<const T*>(src), static_cast<T*>(dst), in[0], in[1],
+                               in[2], out[0], out[1], out[2], (int)zc, (uint32_t)groups,
+                               make_udiv((uint32_t)groups));
+        } else {
+            const RowGrid g = row_grid(out[0], nrows);
+            hipLaunchKernelGGL((resample_cell_kernel<T>), g.grid, g.block, 0, s,
+                               static_cast<const T*>(src), static_cast<T*>(dst), in[0], in[1],
+                               in[2], out[0], out[1], out[2], nrows);
+        }
     }
     return hipGetLastError();
 }
@@ -349,28 +581,32 @@ hipError_t resample_t(const void* src, void* dst, const int32_t in[3], const int
 template <typename T>
 hipError_t flip_t(const void* src, void* dst, const int32_t d[3], int axis, hipStream_t s)
 {
-    const bool inplace = src == dst;
-    // rows per plane and planes iterated (in place along y / z: first half)
-    const int Ys = (inplace && axis == 1) ? d[1] / 2 : d[1];
-    const int Zs = (inplace && axis == 2) ? d[2] / 2 : d[2];
-    const int64_t nrows = (int64_t)Ys * Zs;
-    if (((int64_t)d[0] * sizeof(T)) % 16 == 0 && aligned16(src) && aligned16(dst)) {
-        const int cpr = (int)((int64_t)d[0] * sizeof(T) / 16);
-        const int cs = (inplace && axis == 0) ? (cpr + 1) / 2 : cpr;
-        if (nrows == 0) return hipSuccess;
-        const RowGrid g = row_grid(cs, nrows);
-        hipLaunchKernelGGL((flip_vec_kernel<T>), g.grid, g.block, 0, s,
-                           static_cast<const uint4*>(src), static_cast<uint4*>(dst), cpr, d[1],
-                           d[2], cs, Ys, nrows, axis, inplace ? 1 : 0);
+    constexpr int CPC = 16 / sizeof(T);
+    FlipArgs a{};
+    a.X = d[0];
+    a.Y = d[1];
+    a.Z = d[2];
+    a.axis = axis;
+    a.inplace = src == dst ? 1 : 0;
+    // rows per plane and planes visited (in place along y / z: the first half)
+    const int Ys = a.inplace && axis == 1 ? d[1] / 2 : d[1];
+    const int Zs = a.inplace && axis == 2 ? d[2] / 2 : d[2];
+    int items;
+    if (!a.inplace) {
+        a.nvec = d[0] >= CPC ? (int)(((int64_t)d[0] + CPC - 1) / CPC) : 0;
+        items = a.nvec ? a.nvec : d[0];
+    } else if (axis == 0) {
+        a.nvec = d[0] / (2 * CPC);
+        items = a.nvec + (d[0] - 2 * CPC * a.nvec) / 2;
     } else {
-        const int Xs = (inplace && axis == 0) ? d[0] / 2 : d[0];
-        if (nrows == 0 || Xs == 0) return hipSuccess;  // in place along one cell
-        const RowGrid g = row_grid(Xs, nrows);
-        hipLaunchKernelGGL((flip_kernel<T>), g.grid, g.block, 0, s, static_cast<const T*>(src),
-                           static_cast<T*>(dst), d[0], d[1], d[2], Xs, Ys, nrows, axis,
-                           inplace ? 1 : 0);
+        a.nvec = d[0] / CPC;
+        items = a.nvec + d[0] % CPC;
     }
-    return hipGetLastError();
+    if (Ys == 0 || Zs == 0 || items == 0) return hipSuccess;  // in place along one cell
+    return for_row_boxes(Ys, Zs, items, [&](const RowBox& b, dim3 blocks) {
+        hipLaunchKernelGGL((flip_kernel<T>), blocks, dim3(kNT), 0, s, static_cast<const T*>(src),
+                           static_cast<T*>(dst), a, b);
+    });
 }
 
 }  // namespace
