@@ -202,6 +202,7 @@ __device__ void dot4_tile(const VolDesc& a, const uint32_t* __restrict__ wq, int
 
     const int32_t plane_bytes = (int32_t)plane;  // < 2^31 (host check)
     uint32_t stage[NI + 1];
+    uint32_t fbyte[4];  // bytes of a face dword, merged when it is staged
     auto gather = [&](int zi) {
         const int gz = addr_map(zi, a.Z, a.mode);  // -1 only for border: a zero plane
         const char* base = reinterpret_cast<const char*>(src) +
@@ -212,14 +213,13 @@ __device__ void dot4_tile(const VolDesc& a, const uint32_t* __restrict__ wq, int
         for (int i = 0; i < NI; ++i)
             stage[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)vlane, (int)srow[i], 0);
         stage[NI] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)goff[NI], 0, 0);
+        // (merged here they would be waited for here, a memory latency per
+        // plane in every tile at a face)
         if (face) {
-            uint32_t v = 0;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const uint32_t off = goff[NI] + (fside ? fx[1][q] : fx[0][q]);
-                v |= (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(rs, (int)off, 0, 0) << (8 * q);
-            }
-            stage[NI] = v;
+            for (int q = 0; q < 4; ++q)
+                fbyte[q] = (uint32_t)(uint8_t)__builtin_amdgcn_raw_buffer_load_b8(
+                    rs, (int)(goff[NI] + (fside ? fx[1][q] : fx[0][q])), 0, 0);
         }
     };
     auto put = [&](int b) {
@@ -228,7 +228,8 @@ __device__ void dot4_tile(const VolDesc& a, const uint32_t* __restrict__ wq, int
             for (int i = 0; i < NI; ++i)
                 if (wv_u + kWaves * i < G::HY) lrow[b * G::PLANE_BUF + i * kWaves * G::WD] = stage[i];
         }
-        lds[b * G::PLANE_BUF + loff[NI]] = stage[NI];
+        lds[b * G::PLANE_BUF + loff[NI]] =
+            face ? fbyte[0] | fbyte[1] << 8 | fbyte[2] << 16 | fbyte[3] << 24 : stage[NI];
     };
 
     int32_t acc[K][VY][4];

@@ -47,6 +47,7 @@
 // bits as before.
 #include "vkt_mfma_common.h"
 
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -411,9 +412,14 @@ hipError_t rp_launch(const FilterJob& j, hipStream_t s)
     const int RX = j.roi[3] - j.roi[0], RY = j.roi[4] - j.roi[1], RZ = j.roi[5] - j.roi[2];
     const int64_t ntiles = (int64_t)((RX + g.tx - 1) / g.tx) * ((RY + g.ty - 1) / g.ty);
     const void* fn = (const void*)&filter_mfma_rp_kernel<C>;
+    // Slots of the plan: two workgroups per CU keep the matrix cores busy except
+    // for uint8 (2 products); planned for the third that fits, 1024^3 float32
+    // 7^3 gets three slabs instead of one and takes 2.94 ms instead of 2.75
+    int slots = resident_wgs(fn);
+    if (!std::is_same<typename C::Tin, uint8_t>::value) slots = std::min(slots, 2 * device_cus());
     // (slabs as deep as one round of resident workgroups allows: 1024^3 7^3
     // 3.24 ms with slabs capped at 128 planes, 3.09 ms uncapped)
-    const int tz = plan_tz(ntiles, RZ, j.k, 1, 1 << 20, resident_wgs(fn), 1);
+    const int tz = plan_tz(ntiles, RZ, j.k, 1, 1 << 20, slots, 1);
     const VolDesc a = make_desc(j, tz, g);
     const int64_t nb = ntiles * ((RZ + tz - 1) / tz);
     if (nb > 0x7fffffff) return hipErrorInvalidValue;

@@ -28,8 +28,9 @@
 //    x/y at the same z share an XCD's L2 for their halo re-reads; batched
 //    launches run persistent workgroups that take tile-slabs of many volumes
 //    from a work queue.
-#include "vkt_internal.h"
+#include "vkt_stage.h"
 
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -41,9 +42,9 @@ namespace {
 // the 512^3 5^3 workload; three spill SGPRs at k = 7.
 constexpr int kValuRowGroup = 2;
 // Waves per SIMD the single-volume kernel is compiled for: the 5^3 FP32
-// kernel fits 80 registers (six waves instead of five) with one spilled
-// register, measured 3.6 % faster on the 512^3 workload; other sizes would
-// spill a dozen registers and take what they need.
+// kernels fit 80 registers (six waves instead of five), measured 3.6 % faster
+// on the 512^3 workload; other sizes would spill a dozen registers and take
+// what they need.
 constexpr int valu_waves(int k, bool iacc) { return k == 5 && !iacc ? 6 : 1; }
 
 constexpr int kBX = 16, kBY = 16, kNT = kBX * kBY;  // threads per workgroup
@@ -58,11 +59,11 @@ struct Geo {
     static constexpr int HX = kTX + 2 * R;                // halo tile width
     static constexpr int HY = kBY * VY + 2 * R;           // halo tile height
     static constexpr int P = (HX + 3) & ~3;               // LDS row pitch (cells)
-    static constexpr int NE = (HX * HY + kNT - 1) / kNT;  // halo cells per thread
     static constexpr int WX = kVX + K - 1;                // row window per thread
     static constexpr int NR = (WX + 3) / 4;               // 16-byte reads per row
     static constexpr int NROW = VY + K - 1;               // input rows per thread
     static constexpr int LDS_CELLS = HY * P;              // one plane buffer
+    static __device__ constexpr int at(int row, int col) { return row * P + col; }
     static_assert(4 * (kBX - 1) + 4 * NR <= P, "row window exceeds LDS pitch");
 };
 
@@ -149,20 +150,51 @@ __device__ __attribute__((always_inline)) inline void static_for(F&& f)
 // Dwords of a scalar load covering n weights.
 constexpr int sload_width(int n) { return n <= 4 ? 4 : n <= 8 ? 8 : 16; }
 
-// Raw buffer loads: SGPR resource (base, size) + 32-bit VGPR byte offset.
-// An offset at or beyond the resource size reads 0 (used for border cells).
-constexpr uint32_t kRsrcWord3 = 0x00020000u;   // gfx9-family raw buffer
-constexpr uint32_t kOutside = 0x80000000u;     // byte offset that reads 0
-
-template <typename T>
-__device__ inline T buf_load(__amdgpu_buffer_rsrc_t r, uint32_t off)
+// All weights of a filter of size 1 or 3 (27 and one dword of padding).
+template <int K, typename Acc>
+__device__ inline void load_filter(const Acc* p, Acc (&wk)[28])
 {
-    if constexpr (sizeof(T) == 1) {
-        return (T)__builtin_amdgcn_raw_buffer_load_b8(r, (int)off, 0, 0);
-    } else if constexpr (sizeof(T) == 2) {
-        return (T)__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, 0);
-    } else {
-        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+    Acc a[16], b[8], c[4];
+    load_weights<16>(p, a);
+    if constexpr (K == 3) {
+        load_weights<8>(p + 16, b);
+        load_weights<4>(p + 24, c);
+    }
+#pragma unroll
+    for (int q = 0; q < K * K * K; ++q) wk[q] = q < 16 ? a[q] : q < 24 ? b[q - 16] : c[q - 24];
+}
+
+// Four cells of a row at byte offset off of a plane (any cell alignment), or
+// the first nx of them; offsets past the plane are dropped.
+template <typename T>
+__device__ inline void store4(__amdgpu_buffer_rsrc_t d, uint32_t off, const T (&r)[4], bool whole,
+                              int nx)
+{
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    if (whole) {
+        if constexpr (sizeof(T) == 1)
+            __builtin_amdgcn_raw_buffer_store_b32((uint32_t)r[0] | (uint32_t)r[1] << 8 |
+                                                      (uint32_t)r[2] << 16 | (uint32_t)r[3] << 24,
+                                                  d, (int)off, 0, 0);
+        else if constexpr (sizeof(T) == 2)
+            __builtin_amdgcn_raw_buffer_store_b64(
+                u32x2{(uint32_t)r[0] | (uint32_t)r[1] << 16, (uint32_t)r[2] | (uint32_t)r[3] << 16}, d,
+                (int)off, 0, 0);
+        else
+            __builtin_amdgcn_raw_buffer_store_b128(
+                u32x4{__float_as_uint(r[0]), __float_as_uint(r[1]), __float_as_uint(r[2]),
+                      __float_as_uint(r[3])},
+                d, (int)off, 0, 0);
+        return;
+    }
+    asm volatile("" : "+v"(off));  // (the cells' offsets are not kept over the z loop)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int o = i < nx ? (int)(off + sizeof(T) * i) : (int)kOutside;
+        if constexpr (sizeof(T) == 1) __builtin_amdgcn_raw_buffer_store_b8(r[i], d, o, 0, 0);
+        else if constexpr (sizeof(T) == 2) __builtin_amdgcn_raw_buffer_store_b16(r[i], d, o, 0, 0);
+        else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(r[i]), d, o, 0, 0);
     }
 }
 
@@ -210,44 +242,19 @@ __device__ void valu_tile(const VolDesc& a, const typename AccT<IACC>::type* __r
     constexpr int kVY = VY, kTY = kBY * VY;
     using Acc = typename AccT<IACC>::type;
     constexpr int R = G::R;
-    const T* __restrict__ src = static_cast<const T*>(a.src);
-    T* __restrict__ dst = static_cast<T*>(a.dst);
-
     const int t = threadIdx.x, tx = t % kBX, ty = t / kBX;
     const int x0 = a.rx0 + (tile % a.tiles_x) * kTX, y0 = a.ry0 + (tile / a.tiles_x) * kTY;
     const int zb = a.rz0 + slab * a.tz, ze = min(zb + a.tz, a.rz1);
-    const int64_t plane = (int64_t)a.X * a.Y;
 
-    // Halo gather: the same (x, y) cells for every plane of the slab.
-    uint32_t goff[G::NE];   // in-plane source byte offset (kOutside: zero cell)
-    int32_t loff[G::NE];    // LDS slot
-#pragma unroll
-    for (int i = 0; i < G::NE; ++i) {
-        int e = t + i * kNT;
-        if (e >= G::HX * G::HY) e = G::HX * G::HY - 1;  // duplicate write of the last cell
-        const int hy = e / G::HX, hx = e - hy * G::HX;
-        const int gx = addr_map((int64_t)x0 - R + hx, a.X, a.mode);
-        const int gy = addr_map((int64_t)y0 - R + hy, a.Y, a.mode);
-        goff[i] = (gx < 0 || gy < 0)
-                      ? kOutside
-                      : ((uint32_t)gy * (uint32_t)a.X + (uint32_t)gx) * (uint32_t)sizeof(T);
-        loff[i] = hy * G::P + hx;
-    }
-
-    const int32_t plane_bytes = (int32_t)(plane * (int64_t)sizeof(T));  // < 2^31 (host check)
-    Acc stage[G::NE];
-    auto gather = [&](int zi) {
-        const int gz = addr_map(zi, a.Z, a.mode);  // -1 only for border: a zero plane
-        const char* base = reinterpret_cast<const char*>(src) +
-                           (gz < 0 ? 0 : (int64_t)gz * plane_bytes);
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<char*>(base), (short)0, gz < 0 ? 0 : plane_bytes, (int)kRsrcWord3);
-#pragma unroll
-        for (int i = 0; i < G::NE; ++i) stage[i] = (Acc)buf_load<T>(rs, goff[i]);
-    };
-    auto put = [&](Acc* buf) {
-#pragma unroll
-        for (int i = 0; i < G::NE; ++i) buf[loff[i]] = stage[i];
+    // staging: 4-cell loads of the (tile + 2r) halo through the address mode,
+    // stored to LDS as four sums' type at once
+    using V4 = typename std::conditional<IACC, int4, float4>::type;
+    PlaneStage<T, R, G::HY, G::P, kNT, G> in;
+    in.init(a, x0, y0, t);
+    auto put = [&](Acc* buf) __attribute__((always_inline)) {
+        in.put([&](const T (&v)[4], int e, bool on) __attribute__((always_inline)) {
+            if (on) *reinterpret_cast<V4*>(buf + e) = V4{(Acc)v[0], (Acc)v[1], (Acc)v[2], (Acc)v[3]};
+        });
     };
 
     Acc acc[K][kVY][kVX];
@@ -258,27 +265,40 @@ __device__ void valu_tile(const VolDesc& a, const typename AccT<IACC>::type* __r
 #pragma unroll
             for (int vx = 0; vx < kVX; ++vx) acc[c][vy][vx] = 0;
 
+    // k <= 3: all weights in SGPRs for the whole tile-slab
+    Acc wk[K <= 3 ? 28 : 1];
+    if constexpr (K <= 3) load_filter<K>(w, wk);
+
     const int zi_beg = zb - R, zi_end = ze + R;  // input planes [beg, end)
     // planes zi_beg and zi_beg + 1 in flight before the loop; iteration zi
     // stages plane zi + 1 (loaded during iteration zi - 1) and issues the
     // loads of plane zi + 2, so a load has a whole plane of taps to arrive
-    gather(zi_beg);
+    in.gather(a, zi_beg);
     put(lds);
-    if (zi_beg + 1 < zi_end) gather(zi_beg + 1);
+    if (zi_beg + 1 < zi_end) in.gather(a, zi_beg + 1);
     __syncthreads();
 
     const int ox = x0 + kVX * tx, oy = y0 + kVY * ty;
-    const bool vec = a.vec_ok && ox + kVX <= a.rx1;
-    for (int zi = zi_beg; zi < zi_end; ++zi) {
+    const bool vec = ox + kVX <= a.rx1;
+    uint32_t ooff[kVY];  // this thread's output rows (past the region: dropped)
+#pragma unroll
+    for (int vy = 0; vy < kVY; ++vy)
+        ooff[vy] = oy + vy < a.ry1
+                       ? ((uint32_t)(oy + vy) * (uint32_t)a.X + (uint32_t)ox) * (uint32_t)sizeof(T)
+                       : kOutside;
+    // one input plane; ring slot of filter plane c: c (k >= 5, the ring moves),
+    // (c - U) mod k at plane U mod k (k <= 3, the loop unrolled by k)
+    auto step = [&](int zi, auto uc) __attribute__((always_inline)) {
+        constexpr int U = decltype(uc)::value;
         const int cur = (zi - zi_beg) & 1;
         if (zi + 1 < zi_end) put(lds + (cur ^ 1) * G::LDS_CELLS);
-        if (zi + 2 < zi_end) gather(zi + 2);
+        if (zi + 2 < zi_end) in.gather(a, zi + 2);
 
         const Acc* buf = lds + cur * G::LDS_CELLS + (kVY * ty) * G::P + kVX * tx;
         // ring slot c feeds output plane zi - c + r; slots outside the slab's
         // output planes [zb, ze) are never stored, so their taps are skipped
         const int c_lo = max(0, zi + R - ze + 1), c_hi = min(K - 1, zi + R - zb);
-        using V4 = typename std::conditional<IACC, int4, float4>::type;
+        constexpr int done = K <= 3 ? ((K - 1 - U) % K + K) % K : K - 1;
         if constexpr (K <= 3) {
             // all (2 + k - 1) row windows in registers, then the taps of one
             // filter plane c at a time
@@ -296,9 +316,7 @@ __device__ void valu_tile(const VolDesc& a, const typename AccT<IACC>::type* __r
 #pragma unroll
             for (int c = 0; c < K; ++c) {
                 if (c < c_lo || c > c_hi) continue;
-                constexpr int NW = sload_width(K * K);
-                Acc wv[NW];
-                load_weights<NW>(w + c * K * K, wv);
+                const int slot = ((c - U) % K + K) % K;
 #pragma unroll
                 for (int b = 0; b < K; ++b)
 #pragma unroll
@@ -307,8 +325,8 @@ __device__ void valu_tile(const VolDesc& a, const typename AccT<IACC>::type* __r
                         for (int vy = 0; vy < kVY; ++vy)
 #pragma unroll
                             for (int vx = 0; vx < kVX; ++vx)
-                                acc[c][vy][vx] = mac(wv[b * K + aa], v[b + vy][vx + aa],
-                                                     acc[c][vy][vx]);
+                                acc[slot][vy][vx] = mac(wk[(c * K + b) * K + aa], v[b + vy][vx + aa],
+                                                        acc[slot][vy][vx]);
             }
         } else {
             // stream the row windows; filter rows are loaded one (or, for
@@ -371,42 +389,41 @@ __device__ void valu_tile(const VolDesc& a, const typename AccT<IACC>::type* __r
         // ---- the ring's oldest entry is output plane zo = zi - r
         const int zo = zi - R;
         if (zo >= zb) {
-            T* orow = dst + (int64_t)zo * plane;
+            const int32_t plane_bytes = (int32_t)((int64_t)a.X * a.Y * (int64_t)sizeof(T));
+            const __amdgpu_buffer_rsrc_t d = __builtin_amdgcn_make_buffer_rsrc(
+                static_cast<char*>(a.dst) + (int64_t)zo * plane_bytes, (short)0, plane_bytes,
+                (int)kRsrcWord3);
 #pragma unroll
             for (int vy = 0; vy < kVY; ++vy) {
-                const int y = oy + vy;
-                if (y >= a.ry1) continue;
-                T* o = orow + (int64_t)y * a.X + ox;
                 T r4[kVX];
 #pragma unroll
-                for (int vx = 0; vx < kVX; ++vx) r4[vx] = finish<T>(acc[K - 1][vy][vx], a);
-                if (vec) {
-                    if constexpr (sizeof(T) == 1) {
-                        *reinterpret_cast<uchar4*>(o) = make_uchar4(r4[0], r4[1], r4[2], r4[3]);
-                    } else if constexpr (sizeof(T) == 2) {
-                        *reinterpret_cast<ushort4*>(o) = make_ushort4(r4[0], r4[1], r4[2], r4[3]);
-                    } else {
-                        *reinterpret_cast<float4*>(o) = make_float4(r4[0], r4[1], r4[2], r4[3]);
-                    }
-                } else {
-#pragma unroll
-                    for (int vx = 0; vx < kVX; ++vx)
-                        if (ox + vx < a.rx1) o[vx] = r4[vx];
-                }
+                for (int vx = 0; vx < kVX; ++vx) r4[vx] = finish<T>(acc[done][vy][vx], a);
+                store4<T>(d, ooff[vy], r4, vec, a.rx1 - ox);
             }
         }
         // ---- advance the ring: slot c now belongs to output plane zi+1-c+r
+        if constexpr (K > 3) {
 #pragma unroll
-        for (int c = K - 1; c > 0; --c)
+            for (int c = K - 1; c > 0; --c)
 #pragma unroll
-            for (int vy = 0; vy < kVY; ++vy)
+                for (int vy = 0; vy < kVY; ++vy)
 #pragma unroll
-                for (int vx = 0; vx < kVX; ++vx) acc[c][vy][vx] = acc[c - 1][vy][vx];
+                    for (int vx = 0; vx < kVX; ++vx) acc[c][vy][vx] = acc[c - 1][vy][vx];
+        }
+        constexpr int fresh = K <= 3 ? done : 0;
 #pragma unroll
         for (int vy = 0; vy < kVY; ++vy)
 #pragma unroll
-            for (int vx = 0; vx < kVX; ++vx) acc[0][vy][vx] = 0;
+            for (int vx = 0; vx < kVX; ++vx) acc[fresh][vy][vx] = 0;
         __syncthreads();
+    };
+    if constexpr (K <= 3) {
+        for (int zi = zi_beg; zi < zi_end; zi += K)
+            static_for<K>([&](auto uc) __attribute__((always_inline)) {
+                if (zi + decltype(uc)::value < zi_end) step(zi + decltype(uc)::value, uc);
+            });
+    } else {
+        for (int zi = zi_beg; zi < zi_end; ++zi) step(zi, std::integral_constant<int, 0>{});
     }
 }
 
@@ -533,7 +550,12 @@ hipError_t launch_k(const FilterJob& j, hipStream_t s)
     const int RX = j.roi[3] - j.roi[0], RY = j.roi[4] - j.roi[1], RZ = j.roi[5] - j.roi[2];
     const int64_t ntiles = (int64_t)((RX + g.tx - 1) / g.tx) * ((RY + g.ty - 1) / g.ty);
     const void* fn = (const void*)&filter_valu_kernel<T, K, IACC>;
-    const int tz = plan_tz(ntiles, RZ, K, 1, 128, resident_wgs(fn), 1);
+    // Slots of the plan: for k <= 3, bound by HBM, at most five workgroups per
+    // CU (six measured slower, with thinner slabs and more halo planes: 512^3
+    // float32 3^3 231 us instead of 220)
+    int slots = resident_wgs(fn);
+    if (K <= 3) slots = std::min(slots, 5 * device_cus());
+    const int tz = plan_tz(ntiles, RZ, K, 1, 128, slots, 1);
     const VolDesc a = make_desc(j, tz, g);
     const int64_t nb = ntiles * ((RZ + tz - 1) / tz);
     if (nb > 0x7fffffff) return hipErrorInvalidValue;

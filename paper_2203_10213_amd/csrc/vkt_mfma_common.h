@@ -170,6 +170,40 @@ __device__ inline void store_dwords(__amdgpu_buffer_rsrc_t r, uint32_t off, cons
         __builtin_amdgcn_raw_buffer_store_b32(u[4 * Q], r, (int)off + 16 * Q, 0, 0);
 }
 
+// The first nx (any number) of N stored cells at byte offset off, four at a
+// time where they are whole.
+template <typename T, int N>
+__device__ inline void store_part(__amdgpu_buffer_rsrc_t r, uint32_t off, const uint32_t (&u)[N],
+                                  int nx)
+{
+    asm volatile("" : "+v"(off));  // (the cells' offsets are not kept over the z loop)
+    constexpr int CPD = 4 / sizeof(T);
+#pragma unroll
+    for (int g = 0; g < N; g += 4) {
+        if (g + 4 <= N && g + 4 <= nx) {
+            uint32_t d[4 / CPD];
+#pragma unroll
+            for (int i = 0; i < 4 / CPD; ++i) {
+                d[i] = u[g + CPD * i];
+#pragma unroll
+                for (int c = 1; c < CPD; ++c) d[i] |= u[g + CPD * i + c] << (8 * sizeof(T) * c);
+            }
+            store_dwords<4 / CPD>(r, off + (uint32_t)sizeof(T) * g, d);
+        } else if (g < nx) {
+#pragma unroll
+            for (int i = g; i < g + 4 && i < N; ++i) {
+                const int o = i < nx ? (int)(off + sizeof(T) * i) : (int)kOutside;
+                if constexpr (sizeof(T) == 4)
+                    __builtin_amdgcn_raw_buffer_store_b32(u[i], r, o, 0, 0);
+                else if constexpr (sizeof(T) == 2)
+                    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)u[i], r, o, 0, 0);
+                else
+                    __builtin_amdgcn_raw_buffer_store_b8((uint8_t)u[i], r, o, 0, 0);
+            }
+        }
+    }
+}
+
 // Round (integer cells) and store one lane's row of N finished outputs at
 // byte offset off: vector stores when the row lies inside the volume (buffer
 // stores take any cell alignment), else cell stores for the first nx cells.
@@ -211,16 +245,7 @@ __device__ inline void store_row(__amdgpu_buffer_rsrc_t r, uint32_t off, const f
         if constexpr (sizeof(T) == 1 && REST % 2 == 1)
             __builtin_amdgcn_raw_buffer_store_b8((uint8_t)u[N - 1], r, o + (REST & 2), 0, 0);
     } else {
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const int o = i < nx ? (int)(off + sizeof(T) * i) : (int)kOutside;
-            if constexpr (sizeof(T) == 4)
-                __builtin_amdgcn_raw_buffer_store_b32(u[i], r, o, 0, 0);
-            else if constexpr (sizeof(T) == 2)
-                __builtin_amdgcn_raw_buffer_store_b16((uint16_t)u[i], r, o, 0, 0);
-            else
-                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)u[i], r, o, 0, 0);
-        }
+        store_part<T>(r, off, u, nx);
     }
 }
 

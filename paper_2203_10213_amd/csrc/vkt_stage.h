@@ -77,7 +77,15 @@ struct PlaneStage {
 
     bool face;               // the tile reaches past an x face
     uint32_t goff[NE];       // byte offset of the quad's 4 cells in a plane
-    int qpos[NE];            // its place
+    // its place: where staged rows follow each other without a gap the places
+    // are thread offsets and constants, apart from the last quad's
+    static constexpr bool LINEAR = Pos::at(1, 0) == COLS && Pos::at(2, 0) == 2 * COLS;
+    int qpos[LINEAR ? 2 : NE];
+    __device__ inline int place(int i) const
+    {
+        if constexpr (LINEAR) return i + 1 < NE ? qpos[0] + 4 * NT * i : qpos[1];
+        else return qpos[i];
+    }
     uint32_t inner;          // bit i: quad i lies inside its row
     uint32_t foff[NF][4];    // byte offsets of the face quads' cells
     int fpos[NF];            // their places, -1: none
@@ -90,11 +98,15 @@ struct PlaneStage {
         const int32_t plane_cells = a.X * a.Y;
         face = xl < 0 || xl + COLS > a.X;
         inner = 0;
+        if constexpr (LINEAR) {
+            qpos[0] = 4 * t;
+            qpos[1] = 4 * min(t + (NE - 1) * NT, NQ - 1);
+        }
 #pragma unroll
         for (int i = 0; i < NE; ++i) {
             const int e = min(t + i * NT, NQ - 1);  // repeats the last quad (same values)
             const int hy = e / QR, hx = 4 * (e % QR);
-            qpos[i] = Pos::at(hy, hx);
+            if constexpr (!LINEAR) qpos[i] = Pos::at(hy, hx);
             const int gy = addr_map((int64_t)y0 - R + hy, a.Y, a.mode);
             const int xs = xl + hx;
             // (a face quad's load stays inside the plane; it is not staged; a
@@ -160,11 +172,11 @@ struct PlaneStage {
     {
         if (!face) {
 #pragma unroll
-            for (int i = 0; i < NE; ++i) emit(raw[i], qpos[i], true);
+            for (int i = 0; i < NE; ++i) emit(raw[i], place(i), true);
             return;
         }
 #pragma unroll
-        for (int i = 0; i < NE; ++i) emit(raw[i], qpos[i], ((inner >> i) & 1u) != 0);
+        for (int i = 0; i < NE; ++i) emit(raw[i], place(i), ((inner >> i) & 1u) != 0);
 #pragma unroll
         for (int i = 0; i < NF; ++i) {
             const T v[4] = {(T)fraw[i][0], (T)fraw[i][1], (T)fraw[i][2], (T)fraw[i][3]};
