@@ -328,7 +328,9 @@ vktError vktGetPrecision(vktPrecision* precision);
 vktError vktSetAutotune(int enable);
 
 /* Rank-1 fast path (opt-in, per thread; default: the VKT_SEPARABLE
- * environment variable, "1" enables).  A filter whose weights factor as
+ * environment variable, "1" enables).  (Integer rank-1 filters on integer
+ * cells run in three exact passes without it, where that is faster: the same
+ * sums, on the vector ALUs or as 8-bit dot products as before.)  A filter whose weights factor as
  * w[c][b][a] = t[c] v[b] u[a] -- exactly for integer filters; for float
  * filters every weight to within 2^-20 of itself (so the three passes stay
  * within about 2^-20 sum|w||s| of the dense sum, plus their own FP32

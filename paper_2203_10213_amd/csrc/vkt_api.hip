@@ -312,16 +312,25 @@ vktError create_filter(vktFilter* out, int32_t k, const float* wf, const int32_t
     // rank-1 factors for the separable path
     float* dsep = nullptr;
     Rank1 r1;
-    int64_t sep_sum_abs = 0;
+    int64_t sep_sum_abs = 0, sep_uv_abs = 0;
+    Rank1Int r1i{};
     if (e == hipSuccess) {
         std::vector<double> wd(n);
         for (int i = 0; i < n; ++i) wd[i] = wi ? (double)hi[i] : (double)hf[i];
         r1 = rank1(k, wd, wi != nullptr);
     }
     if (e == hipSuccess && r1.ok) {
-        std::vector<float> hs(3 * 16 + vkt::kWeightPad, 0.f);
+        std::vector<float> hs(2 * 3 * 16 + vkt::kWeightPad, 0.f);
         double su = 0, sv = 0, st = 0;
         for (int i = 0; i < k; ++i) {
+            if (wi) {
+                r1i.u[i] = (int32_t)r1.u[i];
+                r1i.v[i] = (int32_t)r1.v[i];
+                r1i.t[i] = (int32_t)r1.t[i];
+                std::memcpy(&hs[vkt::kSepInt + i], &r1i.u[i], 4);
+                std::memcpy(&hs[vkt::kSepInt + 16 + i], &r1i.v[i], 4);
+                std::memcpy(&hs[vkt::kSepInt + 32 + i], &r1i.t[i], 4);
+            }
             hs[i] = (float)r1.u[i];
             hs[16 + i] = (float)r1.v[i];
             hs[32 + i] = (float)r1.t[i];
@@ -331,6 +340,7 @@ vktError create_filter(vktFilter* out, int32_t k, const float* wf, const int32_t
         }
         const double prod = su * sv * st;
         sep_sum_abs = prod < 9.0e18 ? (int64_t)prod : INT64_MAX;
+        sep_uv_abs = su * sv < 9.0e18 ? (int64_t)(su * sv) : INT64_MAX;
         e = hipMalloc(&dsep, hs.size() * sizeof(float));
         if (e == hipSuccess)
             e = hipMemcpy(dsep, hs.data(), hs.size() * sizeof(float), hipMemcpyHostToDevice);
@@ -354,8 +364,8 @@ vktError create_filter(vktFilter* out, int32_t k, const float* wf, const int32_t
     }
     auto* f = new (std::nothrow) vktFilter_{k, wi != nullptr, wi ? divisor : 1, sum_abs,
                                             wscale, 0, dwf, dwi, dwq, q_ok, q_signed,
-                                            sum_int, m8_ok, dwm, r1.ok, sep_sum_abs, dsep,
-                                            device};
+                                            sum_int, m8_ok, dwm, r1.ok, sep_sum_abs, sep_uv_abs,
+                                            r1i, dsep, device};
     if (!f) {
         (void)hipFree(dwf);
         if (dwi) (void)hipFree(dwi);
@@ -513,10 +523,30 @@ vktError build_job(const vktStructuredVolume_* dst, const vktStructuredVolume_* 
             j.dot4 = false;
         }
     }
+    // Integer rank-1 filters on integer cells as three exact passes, unasked
+    // (the sums are the dense ones): in FP32 below 2^24, else in 24-bit
+    // multiply-adds while the operands of the last pass fit.  From k = 5 on
+    // (dense and in passes: 301x300x300 uint8 5^3 145 and 43 us, 40x41x42 uint16
+    // 5^3 15.3 and 8.0 us); k = 3 only for uint8 (42 and 35 us; uint16
+    // 400x380x360 83 and 85 us) and not where the direct kernel takes it (40x41x42
+    // uint16 5.2 and 5.8 us).  uint8 volumes with 8-bit weights have passes of
+    // their own in the dot-product kernels.
+    const int64_t region =
+        (int64_t)(j.roi[3] - j.roi[0]) * (j.roi[4] - j.roi[1]) * (j.roi[5] - j.roi[2]);
+    if (allow_sep && !j.sep && !j.dot4 && filt->is_int && filt->sep_ok &&
+        src->fmt != vktDataFormatFloat32 &&
+        (filt->k >= 5 ||
+         (filt->k == 3 && src->fmt == vktDataFormatUInt8 && region > (int64_t(1) << 19)))) {
+        const int64_t mx = src->fmt == vktDataFormatUInt8 ? 255 : 65535;
+        j.sep_int = filt->sep_sum_abs >= (int64_t(1) << 24) / mx;
+        j.sep_exact = !j.sep_int || filt->sep_uv_abs < (int64_t(1) << 23) / mx;
+    }
     if (j.dot4) {
         // floor(T/D + 1/2) as round-to-nearest(T * (1/D) + bias); signed
         // weights add the 128 * sum(w) the cells lost by entering as s - 128
         const double D = (double)filt->divisor;
+        j.r1 = allow_sep && filt->sep_ok ? &filt->r1 : nullptr;
+        j.r1_packs = !filt->q_signed && filt->sum_abs_int * 255 < (int64_t(1) << 16);
         j.q_bias = (float)(0.25 / D + (filt->q_signed ? 128.0 * (double)filt->sum_int / D : 0.0));
         // k = 3 with signed 8-bit weights: exact int8 products on the matrix
         // cores (cells always enter as s - 128) when the thread enables them
@@ -751,7 +781,7 @@ vktError vktApplyFilter(vktStructuredVolume dst, vktStructuredVolume src, vktFil
     bool mfma = false, six = false;
     const vktError e = vkt::build_job(dst, src, filt, mode, state().precision, j, mfma, six);
     if (e != vktNoError) return e;
-    if (j.sep) return from_hip(vkt::launch_filter_sep(j, state().stream));
+    if (j.sep || j.sep_exact) return from_hip(vkt::launch_filter_sep(j, state().stream));
     if (mfma) return from_hip(vkt::launch_filter_mfma(j, six, state().stream));
     if (j.i8mma) return from_hip(vkt::launch_filter_i8mma(j, state().stream));
     if (j.dot4) return from_hip(vkt::launch_filter_dot4(j, state().stream));
@@ -772,7 +802,7 @@ vktError vktApplyFilterRange(vktStructuredVolume dst, vktStructuredVolume src, v
         vkt::build_job(dst, src, filt, mode, state().precision, j, mfma, six, roi);
     if (e != vktNoError) return e;
     if (x0 == x1 || y0 == y1 || z0 == z1) return vktNoError;  // empty region
-    if (j.sep) return from_hip(vkt::launch_filter_sep(j, state().stream));
+    if (j.sep || j.sep_exact) return from_hip(vkt::launch_filter_sep(j, state().stream));
     if (mfma) return from_hip(vkt::launch_filter_mfma(j, six, state().stream));
     if (j.i8mma) return from_hip(vkt::launch_filter_i8mma(j, state().stream));
     if (j.dot4) return from_hip(vkt::launch_filter_dot4(j, state().stream));

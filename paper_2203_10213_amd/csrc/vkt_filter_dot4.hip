@@ -133,12 +133,36 @@ __device__ inline void pin8(int32_t (&)[N][4])
     static_assert(N == 1 || N == 2, "rows per lane with scalar weight groups");
 }
 
+// Rank-1 filters w[c][b][a] = t[c] v[b] u[a] (exact integer factors): the dot
+// products run over one filter row, u, and the row sums are summed along y
+// with v and along z with t -- the dense sum, k + k multiply-adds and one row
+// of dot products instead of k^2 rows of them.  kPassPacked: two sums of 16
+// bits per register (unsigned weights with 255 sum(w) < 2^16), kPassInt: one.
+// (512^3 3^3 box: 71 us, dense 80; 400x380x360 5^3 box 56, dense 143; 7^3 box 88,
+// dense 296; with integer sums 3^3 would save nothing.)
+enum Passes { kDense = 0, kPassPacked = 1, kPassInt = 2 };
+struct R1Args {
+    uint32_t u[2];           // packed 8-bit weights of a row
+    uint32_t v[7], t[7];     // kPassPacked: in both halves
+};
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+template <int MODE> struct Sum { typedef int32_t type; };
+template <> struct Sum<kPassPacked> { typedef u16x2 type; };
+__device__ inline u16x2 weight(uint32_t w, u16x2) { return __builtin_bit_cast(u16x2, w); }
+__device__ inline int32_t weight(uint32_t w, int32_t) { return (int32_t)w; }
+__device__ inline u16x2 wmul(u16x2 w, u16x2 x) { return w * x; }
+__device__ inline u16x2 wmac(u16x2 w, u16x2 x, u16x2 s) { return w * x + s; }
+__device__ inline int32_t wmul(int32_t w, int32_t x) { return __mul24(w, x); }
+__device__ inline int32_t wmac(int32_t w, int32_t x, int32_t s) { return __mul24(w, x) + s; }
+
 // One tile-slab: output tile `tile` of z-slab `slab` of volume a.
-template <int K, bool SG, int VYO = 0>
+template <int K, bool SG, int VYO = 0, int MODE = kDense>
 __device__ void dot4_tile(const VolDesc& a, const uint32_t* __restrict__ wq, int tile,
-                          int slab, uint32_t* lds)
+                          int slab, uint32_t* lds, const R1Args& r1 = R1Args{})
 {
     using G = Geo4<K, VYO>;
+    using S = typename Sum<MODE>::type;
+    constexpr int NS = MODE == kPassPacked ? 2 : 4;  // registers of 4 sums
     constexpr int R = G::R, VY = G::VY, NH = G::NH;
     const uint8_t* __restrict__ src = static_cast<const uint8_t*>(a.src);
     uint8_t* __restrict__ dst = static_cast<uint8_t*>(a.dst);
@@ -232,13 +256,13 @@ __device__ void dot4_tile(const VolDesc& a, const uint32_t* __restrict__ wq, int
             face ? fbyte[0] | fbyte[1] << 8 | fbyte[2] << 16 | fbyte[3] << 24 : stage[NI];
     };
 
-    int32_t acc[K][VY][4];
+    S acc[K][VY][NS];
 #pragma unroll
     for (int c = 0; c < K; ++c)
 #pragma unroll
         for (int vy = 0; vy < VY; ++vy)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[c][vy][j] = 0;
+            for (int j = 0; j < NS; ++j) acc[c][vy][j] = S(0);
 
     const int zi_beg = zb - R;
     const int nz = ze - zb;           // output planes of the slab
@@ -266,7 +290,55 @@ __device__ void dot4_tile(const VolDesc& a, const uint32_t* __restrict__ wq, int
         __builtin_amdgcn_s_setprio(1);
         const uint32_t* buf = lds + (p & 1) * G::PLANE_BUF + (wave * VY) * G::WD + lane;
 
-        if constexpr (K <= 3) {
+        if constexpr (MODE != kDense) {
+            S pv[VY][NS];  // this plane's sums over x and y
+#pragma unroll
+            for (int jr = 0; jr < G::NROW; ++jr) {
+                uint32_t L = buf[jr * G::WD], C = buf[jr * G::WD + 1], Rr = buf[jr * G::WD + 2];
+                if constexpr (SG) {
+                    L ^= 0x80808080u;
+                    C ^= 0x80808080u;
+                    Rr ^= 0x80808080u;
+                }
+                int32_t d[4] = {0, 0, 0, 0};
+                static_for<4 * NH>([&](auto qc) {
+                    constexpr int h = decltype(qc)::value / 4, j = decltype(qc)::value % 4;
+                    d[j] = dot4<SG>(window<j - R + 4 * h>(L, C, Rr), r1.u[h], d[j]);
+                });
+                S x[NS];
+                if constexpr (MODE == kPassPacked) {
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        x[j] = __builtin_bit_cast(
+                            u16x2, (uint32_t)d[2 * j] | (uint32_t)d[2 * j + 1] << 16);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) x[j] = d[j];
+                }
+#pragma unroll
+                for (int vy = 0; vy < VY; ++vy) {
+                    const int b = jr - vy;
+                    if (b < 0 || b >= K) continue;
+#pragma unroll
+                    for (int j = 0; j < NS; ++j)
+                        pv[vy][j] = b == 0 ? wmul(weight(r1.v[0], S{}), x[j])
+                                           : wmac(weight(r1.v[b], S{}), x[j], pv[vy][j]);
+                }
+            }
+            static_for<K>([&](auto cc) {
+                constexpr int c = decltype(cc)::value;
+                constexpr int slot = ((U - c) % K + K) % K;
+                // (planes outside the slab are never stored)
+                if (p - c < 0 || p - c >= nz) return;
+#pragma unroll
+                for (int vy = 0; vy < VY; ++vy)
+#pragma unroll
+                    for (int j = 0; j < NS; ++j)
+                        acc[slot][vy][j] = c == 0 ? wmul(weight(r1.t[0], S{}), pv[vy][j])
+                                                  : wmac(weight(r1.t[c], S{}), pv[vy][j],
+                                                         acc[slot][vy][j]);
+            });
+        } else if constexpr (K <= 3) {
             // stream the input rows: the 4 windows of row jr feed every
             // (output row vy, filter row b = jr - vy, filter plane c)
 #pragma unroll
@@ -351,16 +423,21 @@ __device__ void dot4_tile(const VolDesc& a, const uint32_t* __restrict__ wq, int
                 // [0, 255]; no result lies within 1/(4D) of a tie
                 uint32_t packed = 0;
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    packed = __builtin_amdgcn_cvt_pk_u8_f32(
-                        fmaf((float)acc[done][vy][j], inv_D, bias), j, packed);
+                for (int j = 0; j < 4; ++j) {
+                    float sum;
+                    if constexpr (MODE == kPassPacked) sum = (float)acc[done][vy][j / 2][j % 2];
+                    else sum = (float)acc[done][vy][j];
+                    packed = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(sum, inv_D, bias), j, packed);
+                }
                 *reinterpret_cast<uint32_t*>(dst + zo * plane + (int64_t)y * a.X + ox) = packed;
             }
         }
+        if constexpr (MODE == kDense) {
 #pragma unroll
-        for (int vy = 0; vy < VY; ++vy)
+            for (int vy = 0; vy < VY; ++vy)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[done][vy][j] = 0;
+                for (int j = 0; j < 4; ++j) acc[done][vy][j] = 0;
+        }
         __syncthreads();
     };
 
@@ -415,9 +492,55 @@ void filter_dot4_batched_kernel(BatchArgs b)
     }
 }
 
+// Output rows per lane and waves per SIMD of the rank-1 kernels (3^3 with 8
+// rows: 75 us on 512^3, 18.0 on 256^3; with 4 rows 71 and 12.9).
+constexpr int r1_rows(int) { return 4; }
+constexpr int r1_waves(int k, int mode) { return k <= 3 ? 4 : mode == kPassPacked ? 4 : 2; }
+
+template <int K, bool SG, int MODE>
+__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(r1_waves(K, MODE))))
+void filter_dot4_r1_kernel(VolDesc a, R1Args r1, uint32_t nblocks)
+{
+    constexpr int VY = r1_rows(K);
+    __shared__ __align__(16) uint32_t lds[2 * Geo4<K, VY>::PLANE_BUF];
+    const uint32_t lid = xcd_remap(blockIdx.x, nblocks);
+    const uint32_t ntiles = (uint32_t)a.tiles_x * (uint32_t)a.tiles_y;
+    dot4_tile<K, SG, VY, MODE>(a, nullptr, (int)(lid % ntiles), (int)(lid / ntiles), lds, r1);
+}
+
+template <int K, bool SG, int MODE>
+hipError_t launch_r1(const FilterJob& j, hipStream_t s)
+{
+    const ClassGeom g{kTX, kWaves * r1_rows(K), 1};
+    const int RX = j.roi[3] - j.roi[0], RY = j.roi[4] - j.roi[1], RZ = j.roi[5] - j.roi[2];
+    const int64_t ntiles = (int64_t)((RX + g.tx - 1) / g.tx) * ((RY + g.ty - 1) / g.ty);
+    const void* fn = (const void*)&filter_dot4_r1_kernel<K, SG, MODE>;
+    const int tz = plan_tz(ntiles, RZ, K, 1, 128, resident_wgs(fn), K);
+    const VolDesc a = make_desc(j, tz, g);
+    const int64_t nb = ntiles * ((RZ + tz - 1) / tz);
+    if (nb > 0x7fffffff) return hipErrorInvalidValue;
+    R1Args r{};
+    for (int i = 0; i < K; ++i) {
+        const uint32_t both = MODE == kPassPacked ? 0x10001u : 1u;
+        r.u[i / 4] |= ((uint32_t)j.r1->u[i] & 0xffu) << (8 * (i % 4));
+        r.v[i] = (uint32_t)j.r1->v[i] * both;
+        r.t[i] = (uint32_t)j.r1->t[i] * both;
+    }
+    hipLaunchKernelGGL((filter_dot4_r1_kernel<K, SG, MODE>), dim3((unsigned)nb), dim3(kNT), 0, s, a,
+                       r, (uint32_t)nb);
+    return hipGetLastError();
+}
+
+// Dense or, for rank-1 filters (3^3 only where the sums pack), in passes.
 template <int K, bool SG>
 hipError_t launch_k(const FilterJob& j, hipStream_t s)
 {
+    if constexpr (!SG) {
+        if (j.r1 && j.r1_packs) return launch_r1<K, SG, kPassPacked>(j, s);
+    }
+    if constexpr (K > 3) {
+        if (j.r1) return launch_r1<K, SG, kPassInt>(j, s);
+    }
     const ClassGeom g = dot4_geom(K);
     // the output region's tiles and z extent (the whole volume unless a range)
     const int RX = j.roi[3] - j.roi[0], RY = j.roi[4] - j.roi[1], RZ = j.roi[5] - j.roi[2];

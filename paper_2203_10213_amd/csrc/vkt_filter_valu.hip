@@ -164,40 +164,6 @@ __device__ inline void load_filter(const Acc* p, Acc (&wk)[28])
     for (int q = 0; q < K * K * K; ++q) wk[q] = q < 16 ? a[q] : q < 24 ? b[q - 16] : c[q - 24];
 }
 
-// Four cells of a row at byte offset off of a plane (any cell alignment), or
-// the first nx of them; offsets past the plane are dropped.
-template <typename T>
-__device__ inline void store4(__amdgpu_buffer_rsrc_t d, uint32_t off, const T (&r)[4], bool whole,
-                              int nx)
-{
-    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    if (whole) {
-        if constexpr (sizeof(T) == 1)
-            __builtin_amdgcn_raw_buffer_store_b32((uint32_t)r[0] | (uint32_t)r[1] << 8 |
-                                                      (uint32_t)r[2] << 16 | (uint32_t)r[3] << 24,
-                                                  d, (int)off, 0, 0);
-        else if constexpr (sizeof(T) == 2)
-            __builtin_amdgcn_raw_buffer_store_b64(
-                u32x2{(uint32_t)r[0] | (uint32_t)r[1] << 16, (uint32_t)r[2] | (uint32_t)r[3] << 16}, d,
-                (int)off, 0, 0);
-        else
-            __builtin_amdgcn_raw_buffer_store_b128(
-                u32x4{__float_as_uint(r[0]), __float_as_uint(r[1]), __float_as_uint(r[2]),
-                      __float_as_uint(r[3])},
-                d, (int)off, 0, 0);
-        return;
-    }
-    asm volatile("" : "+v"(off));  // (the cells' offsets are not kept over the z loop)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int o = i < nx ? (int)(off + sizeof(T) * i) : (int)kOutside;
-        if constexpr (sizeof(T) == 1) __builtin_amdgcn_raw_buffer_store_b8(r[i], d, o, 0, 0);
-        else if constexpr (sizeof(T) == 2) __builtin_amdgcn_raw_buffer_store_b16(r[i], d, o, 0, 0);
-        else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(r[i]), d, o, 0, 0);
-    }
-}
-
 template <bool IACC> struct AccT { using type = float; };
 template <> struct AccT<true> { using type = int32_t; };
 

@@ -20,6 +20,11 @@ struct vktStructuredVolume_ {
     int device;
 };
 
+// Integer factors of a rank-1 integer filter: w[c][b][a] = t[c] v[b] u[a].
+struct Rank1Int {
+    int32_t u[15], v[15], t[15];
+};
+
 struct vktFilter_ {
     int32_t k;
     bool is_int;
@@ -38,10 +43,13 @@ struct vktFilter_ {
     // plane c the x-Toeplitz W_c as 64 lanes x 16 signed bytes
     bool m8_ok;
     uint32_t* d_wm;
-    // rank-1 factors (u over x | v over y | t over z, 16 floats each) with
-    // u (x) v (x) t = w (exactly, with integer factors, for integer filters)
+    // rank-1 factors (u over x | v over y | t over z, 16 floats each, then
+    // 16 integers each) with u (x) v (x) t = w (exactly, with integer factors,
+    // for integer filters)
     bool sep_ok;
     int64_t sep_sum_abs;        // sum|u| sum|v| sum|t|
+    int64_t sep_uv_abs;         // sum|u| sum|v|
+    Rank1Int r1;                // the factors of integer filters
     float* d_sep;
     int device;
 };
@@ -70,6 +78,8 @@ UDiv make_udiv(uint32_t d);
 // many zero dwords, so that a wide scalar load of the last weight group stays
 // inside the allocation.
 constexpr int kWeightPad = 16;
+// Dwords before the integer factors of a rank-1 filter's device buffer.
+constexpr int kSepInt = 48;
 
 // Everything one single-volume ApplyFilter launch needs.
 struct FilterJob {
@@ -93,11 +103,15 @@ struct FilterJob {
     bool q_signed;           // signed 8-bit weights (cells enter as s - 128)
     const uint32_t* wq;      // device packed weights
     float q_bias;            // epilogue constant of the dot-product path
+    const Rank1Int* r1;      // factors of a rank-1 filter on it (host), or null
+    bool r1_packs;           // its sums fit 16 bits, unsigned
     bool i8mma;              // uint8 cells, k = 3, int8 matrix-core path
     const uint32_t* wm;      // device W operands of that path
     float m8_bias;           // its epilogue constant: (1/4 + 128 sum(w)) / D
     bool sep;                // rank-1 filter on the separable path
-    const float* wsep;       // device factors u | v | t (16 floats each)
+    const float* wsep;       // device factors u | v | t (16 floats, then integers each)
+    bool sep_exact;          // integer rank-1 filter on integer cells, unasked: exact
+    bool sep_int;            // the passes in 24-bit multiply-adds and int32 sums
 };
 
 // Stored-result rule of an ApplyFilter.
