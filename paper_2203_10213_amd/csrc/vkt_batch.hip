@@ -126,12 +126,6 @@ void tune_store_locked()
     std::fclose(f);
 }
 
-int default_tz(const ClassKey& c, const ClassGeom& g)
-{
-    (void)c;
-    return std::max(g.tz_min, 16);
-}
-
 // ---- plans ------------------------------------------------------------------
 
 struct ClassPlan {
@@ -242,6 +236,28 @@ TuneVal tuned(const TuneKey& tk)
     tune_load_locked();
     auto it = g_tune.find(tk);
     return it != g_tune.end() ? it->second : TuneVal{0, 0};
+}
+
+// Slab depth where the table has no entry.  Each slab reads and multiplies k - 1
+// planes besides its own, so the matrix-core classes take 64 planes where that
+// still leaves an item for each CU (the classes run side by side, so that one
+// class's tail is filled by another's items).  Against 16 planes (20 and 28 for
+// k = 5 and 7): 256 uint16 volumes of 32 to 256 2450 -> 2270 us, 128 float32 of 40
+// to 160 769 -> 730 us, 48 of 64 to 180 553 -> 529 us, 24 uint8 of 96 to 256
+// 446 -> 433 us.  With the line at four items per CU the last three stayed as
+// they were.  The vector classes, whose planes cost less, keep 16.
+int default_tz(const std::vector<Triple>& tr, const ClassPlan& cp, const ClassGeom& g)
+{
+    constexpr int kDeep = 64;
+    const int base = std::max(g.tz_min, 16);
+    if (cp.key.path != 1 || base >= kDeep) return base;
+    int64_t n = 0;
+    for (int idx : cp.members) {
+        const FilterJob& j = tr[idx].j;
+        n += (int64_t)((j.X + g.tx - 1) / g.tx) * ((j.Y + g.ty - 1) / g.ty) *
+             ((j.Z + kDeep - 1) / kDeep);
+    }
+    return n >= (int64_t)device_cus() ? kDeep : base;
 }
 
 // Build (or rebuild for another slab depth) the host-side arrays of one class.
@@ -433,7 +449,7 @@ vktError build_plan(const std::vector<Triple>& tr, std::vector<uintptr_t>&& sig,
         }
         cp.variant = tv.tz > 0 ? tv.variant : 0;
         const ClassGeom geom = class_geom(cp.key, cp.variant);
-        cp.tz = std::max(tv.tz > 0 ? tv.tz : default_tz(cp.key, geom), geom.tz_min);
+        cp.tz = std::max(tv.tz > 0 ? tv.tz : default_tz(tr, cp, geom), geom.tz_min);
         cp.func = class_kernel(cp.key, cp.variant);
         int per_cu = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, cp.func, 256, 0) !=
@@ -602,41 +618,53 @@ vktError batched_no_alloc(const std::vector<Triple>& tr, hipStream_t stream)
     std::vector<std::vector<WorkItem>> items(groups.size());
     std::vector<size_t> npool(groups.size());
     // layout: the heads of all classes (descriptors, work list, counters),
-    // then the weight pools
-    size_t bytes = 0, c = 0;
-    for (auto& g : groups) {
-        ClassPlan cp;
-        cp.key = g.first;
-        cp.members = g.second;
-        const TuneVal tv = tuned(tune_key(tr, cp));
-        cp.variant = tv.tz > 0 ? tv.variant : 0;
-        cp.func = class_kernel(cp.key, cp.variant);
-        if (!cp.func) return vktUnsupported;
-        const ClassGeom geom = class_geom(cp.key, cp.variant);
-        cp.tz = std::max(tv.tz > 0 ? tv.tz : default_tz(cp.key, geom), geom.tz_min);
-        std::vector<float> wf;
-        std::vector<int32_t> wi;
-        class_arrays(tr, cp, descs[c], items[c], wf, wi);
-        const size_t n3 = (size_t)class_weights(cp.key);
-        for (const auto& d : descs[c]) npool[c] = std::max(npool[c], (size_t)d.woff / n3 + 1);
-        cp.off_desc = bytes = align_up(bytes, 256);
-        bytes += descs[c].size() * sizeof(VolDesc);
-        cp.off_items = bytes = align_up(bytes, 256);
-        bytes += items[c].size() * sizeof(WorkItem);
-        cp.off_cnt = bytes = align_up(bytes, 256);
-        bytes += 2 * sizeof(uint32_t);
-        cp.grid = (unsigned)resident_wgs(cp.func);
-        classes.push_back(cp);
-        ++c;
-    }
-    for (size_t i = 0; i < classes.size(); ++i) {
-        ClassPlan& cp = classes[i];
-        const size_t n3 = (size_t)class_weights(cp.key);
-        cp.off_wf = bytes = align_up(bytes, 256);
-        bytes += (npool[i] * n3 + kWeightPad) * sizeof(float);
-        cp.off_wi = bytes = align_up(bytes, 256);
-        bytes += (npool[i] * n3 + kWeightPad) * sizeof(int32_t);
-    }
+    // then the weight pools; returns the bytes it takes (0: no kernel)
+    auto lay_out = [&](bool taller) -> size_t {
+        size_t bytes = 0, c = 0;
+        classes.clear();
+        for (auto& g : groups) {
+            ClassPlan cp;
+            cp.key = g.first;
+            cp.members = g.second;
+            const TuneVal tv = tuned(tune_key(tr, cp));
+            cp.variant = tv.tz > 0 ? tv.variant : 0;
+            if (taller && class_geom(cp.key, 1 - cp.variant).ty > class_geom(cp.key, cp.variant).ty)
+                cp.variant = 1 - cp.variant;
+            cp.func = class_kernel(cp.key, cp.variant);
+            if (!cp.func) return 0;
+            const ClassGeom geom = class_geom(cp.key, cp.variant);
+            cp.tz = std::max(tv.tz > 0 ? tv.tz : default_tz(tr, cp, geom), geom.tz_min);
+            std::vector<float> wf;
+            std::vector<int32_t> wi;
+            class_arrays(tr, cp, descs[c], items[c], wf, wi);
+            const size_t n3 = (size_t)class_weights(cp.key);
+            npool[c] = 0;
+            for (const auto& d : descs[c]) npool[c] = std::max(npool[c], (size_t)d.woff / n3 + 1);
+            cp.off_desc = bytes = align_up(bytes, 256);
+            bytes += descs[c].size() * sizeof(VolDesc);
+            cp.off_items = bytes = align_up(bytes, 256);
+            bytes += items[c].size() * sizeof(WorkItem);
+            cp.off_cnt = bytes = align_up(bytes, 256);
+            bytes += 2 * sizeof(uint32_t);
+            cp.grid = (unsigned)resident_wgs(cp.func);
+            classes.push_back(cp);
+            ++c;
+        }
+        for (size_t i = 0; i < classes.size(); ++i) {
+            ClassPlan& cp = classes[i];
+            const size_t n3 = (size_t)class_weights(cp.key);
+            cp.off_wf = bytes = align_up(bytes, 256);
+            bytes += (npool[i] * n3 + kWeightPad) * sizeof(float);
+            cp.off_wi = bytes = align_up(bytes, 256);
+            bytes += (npool[i] * n3 + kWeightPad) * sizeof(int32_t);
+        }
+        return bytes;
+    };
+    size_t bytes = lay_out(false);
+    // taller tiles make fewer items (6-product float32 13^3 and 15^3 run on the
+    // shorter ones, which halves the rows that the scratch holds items for)
+    if (bytes > kNoAllocBytes) bytes = lay_out(true);
+    if (bytes == 0) return vktUnsupported;
     if (bytes > kNoAllocBytes) return vktUnsupported;  // the batch does not fit
 
     std::lock_guard<std::mutex> lk(nd->mu);
