@@ -67,21 +67,25 @@ template <> struct Mf<32> {
 template <typename T, int K, int PM, int SYV = 0>
 struct Cfg {
     using Tin = T;
+    // the same kernel on one row block, for small volumes (16x16 tiles)
+    using Short = Cfg<T, K, PM, SYV == 0 && K <= 7 ? 1 : SYV>;
     using PC = Pieces<PM>;
     static constexpr int SHAPE = K <= 7 ? 16 : 32;
     using M = Mf<SHAPE>;
     static constexpr int R = (K - 1) / 2;
-    // output columns per strip
-    static constexpr int NX = K == 5 || (K == 9 && std::is_same<T, float>::value) ? 3 : 2;
+    // output columns per strip (two on the short 16x16 tile: 32 columns, not 48,
+    // for small volumes)
+    static constexpr int NX =
+        (K == 5 && SYV != 1) || (K == 9 && std::is_same<T, float>::value) ? 3 : 2;
     static_assert(K * NX <= M::NT, "column groups exceed the tile");
     static_assert(NX + K - 1 <= M::AXW, "x window exceeds the K slots");
     static constexpr int NCH = SHAPE == 16 ? (K + 3) / 4 : K;      // K chunks
     static constexpr int SX = 16;                                   // strips per workgroup
     static constexpr int WS = 4;                                    // strips per wave
     static_assert(SX == 4 * WS, "four waves");
-    // row blocks per workgroup: two 16-row blocks (with four the kernels
-    // needed a third more registers, two waves per SIMD instead of three or
-    // four, and measured 5-8 % slower), one 32-row block
+    // row blocks per workgroup: two 16-row blocks (one for small volumes: Short;
+    // with four the kernels needed a third more registers, two waves per SIMD
+    // instead of three or four, and measured 5-8 % slower), one 32-row block
     // segment reads of the next (row block, K chunk) group issued before the
     // current group's products: on 16x16 tiles, for uint16 and for 3-product
     // float32 9^3 (224 registers, no spills; 1024^3 12.45 -> 11.77 ms, 512^3
@@ -182,6 +186,15 @@ __device__ void mfma_tile(const VolDesc& a, const float* __restrict__ w, int til
     const int32_t plane_bytes = (int32_t)(plane * (int64_t)sizeof(T));  // < 2^31 (host check)
     const int jcol = lane % M::NT, gq = lane / M::NT;
 
+    // ---- staging of the input plane: COLS x HY cells from (x0 - r, y0 - r).  The
+    // first plane's loads go out before the weights are read and split, one
+    // memory latency less in front of a small volume's few planes
+    // (94x91x97 float32 5^3 19.05 -> 17.6 us).
+    const int zi_beg = zb - R, zi_end = ze + R;
+    PlaneStage<T, R, C::HY, C::COLS, kNT, C> in;
+    in.init(a, x0, y0, t);
+    in.gather(a, zi_beg);
+
     // ---- B operand: x-Toeplitz band of each filter row, split into pieces;
     // b: filter row, ax0: the first of its 8 input columns
     auto weights = [&](int c, int xo, int b, int ax0, u16x8 (&v)[PC::NBI]) {
@@ -220,10 +233,7 @@ __device__ void mfma_tile(const VolDesc& a, const float* __restrict__ w, int til
         for (int q = 0; q < C::NCH; ++q) weights(jcol / NX, jcol % NX, q * 4 + gq, 0, B[q]);
     }
 
-    // ---- staging of the input plane: COLS x HY cells from (x0 - r, y0 - r);
     // staged columns past X + r meet zero weights: they hold zeros
-    PlaneStage<T, R, C::HY, C::COLS, kNT, C> in;
-    in.init(a, x0, y0, t);
     if (in.face) {
         for (int e = t; e < 2 * PC::PS * C::PLANE / 8; e += kNT)
             reinterpret_cast<u32x4*>(lds_base)[e] = u32x4{0u, 0u, 0u, 0u};
@@ -261,8 +271,6 @@ __device__ void mfma_tile(const VolDesc& a, const float* __restrict__ w, int til
     // Before plane zi's products plane zi is in LDS and the loads of plane
     // zi + 1 are in flight; it is staged after the products, and the loads of
     // plane zi + 2 take its registers at once (a whole step to arrive).
-    const int zi_beg = zb - R, zi_end = ze + R;
-    in.gather(a, zi_beg);
     put(0);
     in.gather(a, min(zi_beg + 1, zi_end - 1));
     __syncthreads();
@@ -479,13 +487,22 @@ hipError_t launch_cfg(const FilterJob& j, hipStream_t s)
     // the output region's tiles and z extent (the whole volume unless a range)
     const int RX = j.roi[3] - j.roi[0], RY = j.roi[4] - j.roi[1], RZ = j.roi[5] - j.roi[2];
     const int64_t ntiles = (int64_t)((RX + g.tx - 1) / g.tx) * ((RY + g.ty - 1) / g.ty);
+    // Volumes that do not make two workgroups per CU even with one-plane slabs
+    // take the 16x16 tile of one row block: twice the workgroups, half the step
+    // of each, two-column strips for k = 5 (64^3 uint8, uint16, float32 5^3 8.4,
+    // 10.5 and 12.5 -> 6.9, 8.1 and 9.6 us; 40^3 7^3 9.3, 12.5 and 15 -> 7.4, 8.9
+    // and 9.9 us).
+    using Short = typename C::Short;
+    if constexpr (!std::is_same<Short, C>::value)
+        if (ntiles * RZ < 2 * (int64_t)device_cus()) return launch_cfg<Short>(j, s);
     const void* fn = (const void*)&filter_mfma_kernel<C>;
-    // Slots of the plan: the workgroups that fill the device once.  32x32 tiles
-    // keep the matrix cores busy with two workgroups per CU; planned for the
-    // three or four that fit, a small volume gets thinner slabs with more halo
-    // planes for nothing (150x141x133 uint16 11^3: 157 us, for two 136 us).
-    int slots = resident_wgs(fn);
-    if (C::SHAPE == 32) slots = std::min(slots, 2 * device_cus());
+    // Slots of the plan: the workgroups that fill the device once, at most two
+    // per CU, which keep the matrix cores busy; planned for the three or four
+    // that fit, a small volume gets thinner slabs with more halo planes for
+    // nothing (150x141x133 uint16 11^3: 157 us, for two 136 us; 144x131x127 uint8,
+    // uint16 and float32 5^3 15.5, 22.3 and 34 us, for two 13.1, 18.4 and 24.6;
+    // 7^3 21.8, 33.6 and 41 us, for two 17.6, 24.2 and 31.8).
+    const int slots = std::min(resident_wgs(fn), 2 * device_cus());
     // (deeper slabs measured slower for the 16x16 tiles, faster for 32x32)
     const int tz = plan_tz(ntiles, RZ, j.k, 1, C::SHAPE == 16 ? 128 : 512, slots, 1);
     const VolDesc a = make_desc(j, tz, g);
