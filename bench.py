@@ -132,15 +132,16 @@ def make_cases(name, device, precision, compare):
 
 KERNEL_SOURCES = {
     "resample": ["vkt_resample.hip", "vkt_internal.h"],
-    "valu": ["vkt_filter_valu.hip", "vkt_internal.h"],
+    "valu": ["vkt_filter_valu.hip", "vkt_stage.h", "vkt_internal.h"],
     "dot4": ["vkt_filter_dot4.hip", "vkt_internal.h"],
     "i8mma": ["vkt_filter_i8mma.hip", "vkt_internal.h"],
-    "mfma": ["vkt_filter_mfma.hip", "vkt_filter_mfma_rp.hip", "vkt_mfma_common.h", "vkt_internal.h"],
-    "sep": ["vkt_filter_sep.hip", "vkt_internal.h"],
+    "mfma": ["vkt_filter_mfma.hip", "vkt_filter_mfma_rp.hip", "vkt_mfma_common.h", "vkt_stage.h",
+             "vkt_internal.h"],
+    "sep": ["vkt_filter_sep.hip", "vkt_stage.h", "vkt_internal.h"],
     # the batched graph: its planner and every class kernel it may launch
     "batched": ["vkt_batch.hip", "vkt_filter_valu.hip", "vkt_filter_dot4.hip",
                 "vkt_filter_mfma.hip", "vkt_filter_mfma_rp.hip", "vkt_mfma_common.h",
-                "vkt_internal.h"],
+                "vkt_stage.h", "vkt_internal.h"],
 }
 
 

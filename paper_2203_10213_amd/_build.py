@@ -26,7 +26,7 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
 # in VGPRs: the 16x16 build so that the per-plane lane shift needs no copies;
 # the 32x32 build because it then needs no accumulator copies either (1024^3
 # 9^3 float32 13.45 -> 13.07 ms, 2048x2048x1024 11^3 uint16 75.5 -> 71.7 ms,
-# and fewer registers: the 11^3 uint16 kernel 435 -> 321).
+# and fewer registers).
 VARIANTS = {
     "vkt_filter_mfma.hip": [
         ("vkt_filter_mfma16", ["-DVKT_MFMA_SHAPE=16", "-mllvm", "--amdgpu-mfma-vgpr-form"]),

@@ -430,7 +430,6 @@ VolDesc make_desc(const FilterJob& j, int tz, ClassGeom g)
     a.D = j.D;
     a.div2D = j.div2D;
     a.inv_D = j.inv_D;
-    a.vec_ok = j.vec_store ? 1 : 0;
     a.wscale = j.fmt == vktDataFormatFloat32 ? 1.0f : j.wscale;  // bf16 pieces are unscaled
     a.unscale = 1.0f / a.wscale;
     a.bias = j.q_bias;
@@ -479,10 +478,6 @@ vktError build_job(const vktStructuredVolume_* dst, const vktStructuredVolume_* 
         j.int_acc = filt->sum_abs_int * mx >= (int64_t(1) << 24);
         j.div2D = make_udiv(2u * (uint32_t)filt->divisor);
     }
-    // 4-cell vector stores: rows, the region's first column and the buffer
-    // 4-cell aligned
-    j.vec_store = (j.X % 4 == 0) && (j.roi[0] % 4 == 0) &&
-                  (reinterpret_cast<uintptr_t>(dst->dev) % (4 * cell_bytes(src->fmt)) == 0);
     j.wscale = filt->wscale;
     // Plan: float-weight filters with k >= 5 run on the matrix cores unless
     // the precision is FP32; everything else (k < 5, integer weights, whose

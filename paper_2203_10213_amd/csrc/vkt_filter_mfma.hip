@@ -85,18 +85,18 @@ struct Cfg {
     static_assert(SX == 4 * WS, "four waves");
     // row blocks per workgroup: two 16-row blocks (one for small volumes: Short;
     // with four the kernels needed a third more registers, two waves per SIMD
-    // instead of three or four, and measured 5-8 % slower), one 32-row block
-    // segment reads of the next (row block, K chunk) group issued before the
+    // instead of three or four, and measured 5-8 % slower), one 32-row block.
+    // PIPE: segment reads of the next (row block, K chunk) group issued before the
     // current group's products: on 16x16 tiles, for uint16 and for 3-product
-    // float32 9^3 (224 registers, no spills; 1024^3 12.45 -> 11.77 ms, 512^3
-    // 1.66 -> 1.58 ms, bit-identical).  The other 32x32 kernels read each
+    // float32 9^3 (no spills; with two-column strips 1024^3 12.45 -> 11.77 ms,
+    // 512^3 1.66 -> 1.58 ms, bit-identical).  The other 32x32 kernels read each
     // group's segments just before its products: uint8 9^3 / 11^3 measured 1 %
     // slower pipelined, float32 11^3 the same, and 6-product float32 spills.
     static constexpr bool PIPE = SHAPE == 16 || std::is_same<T, uint16_t>::value ||
                                  (std::is_same<T, float>::value && PM != kF32x6 && K <= 9);
     static constexpr int SY_DEFAULT = SHAPE == 16 ? 2 : 1;
     static constexpr int SY = SYV ? SYV : SY_DEFAULT;
-    static constexpr int TX = SX * NX, TY = SY * M::MT;             // 32 x 32 or 32 x 64 tile
+    static constexpr int TX = SX * NX, TY = SY * M::MT;
     static constexpr int WX = WS * NX;                              // columns per wave
     // dwords of a lane's segment: the 8-column windows of the wave's strips,
     // read 8 bytes (24-byte wave offsets) or 16 bytes at a time

@@ -96,7 +96,6 @@ struct FilterJob {
     int32_t D;
     UDiv div2D;              // for 2*D
     float inv_D;             // 1/D for float outputs of integer filters
-    bool vec_store;          // dst rows can take 16-B-aligned vector stores
     float wscale;            // 2^s with max|w| * 2^s in [2^14, 2^15) (fp16 splitting)
     int32_t roi[6];          // output region [x0, y0, z0, x1, y1, z1)
     bool dot4;               // uint8 cells, 8-bit packed integer weights
@@ -138,7 +137,6 @@ struct VolDesc {
     int32_t D;
     UDiv div2D;
     float inv_D;
-    int32_t vec_ok;
     float wscale, unscale;   // fp16 weight scaling of the matrix-core path
     float bias;              // dot-product path: 1/(4D) (+ 128 sum(w) / D)
     int32_t rx0, ry0, rz0;   // output region: tiles start here ...
