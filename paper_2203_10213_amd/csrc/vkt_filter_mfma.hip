@@ -10,7 +10,8 @@
 //
 // GEMM embedding, per input plane zi (D += A * B on MFMA tiles):
 //   M (rows i)    : consecutive output rows y_i of one x-strip of NX output
-//                   columns (3 for k = 5 and float32 k = 9, else 2),
+//                   columns (3 for k = 5 and float32 k = 9, else 2; 2 for k = 5
+//                   on the short tile of small volumes),
 //   K (reduction) : (filter row b, input column ax) pairs; the A operand is
 //                   the input window s(x_s - r + ax, y_i + b - r, zi), read
 //                   straight from the LDS-staged plane (no im2col copy),

@@ -20,9 +20,9 @@
 //    After the plane, the ring's oldest entry is a finished output: it is
 //    rounded, stored, and the ring advances.
 //  * Weights are uniform: they are scalar operands of the multiply-adds,
-//    loaded one group (a filter plane for k = 3, the rows (c, b), (c+1, b)
-//    for k = 5, 7, else a filter row) at a time with explicit scalar loads
-//    and one wait per group.  For k >= 5 the row windows stream through
+//    for k <= 3 all held over the slab, else loaded one group (the rows (c, b),
+//    (c+1, b) for k = 5, 7, else a filter row) at a time with explicit scalar
+//    loads and one wait per group.  For k >= 5 the row windows stream through
 //    registers one input row at a time.
 //  * Single-volume launches number workgroups XCD-aware so tiles adjacent in
 //    x/y at the same z share an XCD's L2 for their halo re-reads; batched
