@@ -138,7 +138,7 @@ KERNEL_SOURCES = {
     "mfma": ["vkt_filter_mfma.hip", "vkt_filter_mfma_rp.hip", "vkt_mfma_common.h", "vkt_stage.h",
              "vkt_internal.h"],
     "sep": ["vkt_filter_sep.hip", "vkt_stage.h", "vkt_internal.h"],
-    # the batched graph: its planner and every class kernel it may launch
+    # the batched call: its planner and every class kernel it may launch
     "batched": ["vkt_batch.hip", "vkt_filter_valu.hip", "vkt_filter_dot4.hip",
                 "vkt_filter_mfma.hip", "vkt_filter_mfma_rp.hip", "vkt_mfma_common.h",
                 "vkt_stage.h", "vkt_internal.h"],
@@ -442,8 +442,8 @@ def copy_probe():
 
 def run_batched(args, vkt, torch):
     """The batched workload: 256 uint16 volumes of uneven sizes, k in {3,5,7}
-    Gaussians, one vktApplyFilterBatched (persistent kernels, replayed
-    hipGraph) per step.  Timed three ways: the batched call with the planner's
+    Gaussians, one vktApplyFilterBatched (persistent kernels, cached
+    plan) per step.  Timed three ways: the batched call with the planner's
     default slab depths, the batched call after the autotuner has timed its
     candidates on this batch (a second set of outputs, so a second plan), and
     the same work as 256 single launches.  The CPU leg times the oracle on one

@@ -199,16 +199,19 @@ vktError vktApplyFilterRange(vktStructuredVolume dst, vktStructuredVolume src,
  * sizes and filters of different k.  The pairs are grouped into arithmetic
  * classes (format, k, path); each class runs as one persistent launch whose
  * workgroups take tile-slabs of all its volumes from a work queue, longest
- * first; the class launches are the parallel nodes of one hipGraph that is
- * launched on the calling thread's stream.  The plan (descriptors, work lists,
- * weight pools, graph) is cached per batch signature -- volume pointers and
- * dims, filter identities, mode, precision and stream -- so a repeated batch
- * is one graph launch.  Outputs must not overlap any volume of the batch.
+ * first; the class launches run side by side, on streams of the plan that fork
+ * from the calling thread's stream and join it again.  The plan (descriptors,
+ * work lists, weight pools, streams) is cached per batch signature -- volume
+ * pointers and dims, filter identities, mode, precision and stream; the 16 last
+ * used are kept -- so a repeated batch is its launches alone.  While the stream
+ * is being captured a batch whose plan is cached is recorded into the graph (and
+ * its plan is kept until the process ends); without a cached plan the call
+ * allocates memory, which a capture may refuse.  Outputs must not overlap any volume of the batch.
  * Two calls with the same signature must not run concurrently (they share
  * the plan's work queue).  Calls from several threads are serialised inside
- * the library (planning, graph instantiation and launch run one call at a
- * time; the enqueued work runs concurrently on the callers' streams).  With vktSetAutotune(1) the first plan of a batch
- * size class times, per class, both tile heights of the class kernel at
+ * the library (planning and launch run one call at a time; the enqueued work
+ * runs concurrently on the callers' streams).  With vktSetAutotune(1) the first
+ * plan of a batch size class times, per class, both tile heights of the class kernel at
  * candidate z-slab depths on the real data (this writes the outputs and
  * waits for the stream) and records the fastest tile and depth;
  * VKT_TUNE_CACHE=<file> keeps that table across processes.

@@ -12,11 +12,11 @@
 //     tile height at candidate depths on the real batch); the class's work
 //     list is sorted longest first;
 //   * descriptors, work lists, the classes' weight pools and the work-queue
-//     counters go to one device buffer; the class kernels become parallel
-//     kernel nodes of one hipGraph.
-// Launch: one hipGraphLaunch on the calling thread's stream.  Plans are cached
-// by the batch's signature (pointers, dims, formats, filter identities, mode,
-// precision, stream), so repeated batches replay the instantiated graph.
+//     counters go to one device buffer.
+// Launch: the class kernels side by side, on streams of the plan that fork from
+// the calling thread's stream and join it again.  Plans are cached by
+// the batch's signature (pointers, dims, formats, filter identities, mode,
+// precision, stream), so a repeated batch is its launches alone.
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
@@ -135,11 +135,61 @@ struct ClassPlan {
     int tz = 0;
     int variant = 0;               // tile-height variant
     unsigned grid = 0;
+    size_t lane = 0;               // side stream it runs on; past them: the caller's
     BatchArgs args{};
     // offsets inside the plan's device buffer
     size_t off_desc = 0, off_items = 0, off_cnt = 0, off_wf = 0, off_wi = 0;
     uint32_t nitems = 0;
 };
+
+// The streams on which a plan's classes run beside its caller's, with the
+// events that fork and join them.  A plan has a set of its own: shared by the
+// plans of two callers, a set would make one caller's kernels wait for the
+// other's stream.  Sets go back to a free list with their plan, so there are
+// no more than plans alive at once (the cache, the one that is made and the
+// captured ones), and are never destroyed.
+constexpr size_t kSideStreams = 3;  // (with the caller's, the 4 hardware queues)
+struct SideStreams {
+    int device = 0;
+    hipEvent_t fork = nullptr;
+    hipStream_t stream[kSideStreams] = {};
+    hipEvent_t joined[kSideStreams] = {};
+    size_t n = 0;
+};
+std::mutex g_side_mu;
+std::vector<std::unique_ptr<SideStreams>> g_side_free;
+
+// A set of n streams of the current device `dev`; null where they cannot be
+// made (the classes then run one after another).
+std::unique_ptr<SideStreams> take_side_streams(int dev, size_t n)
+{
+    std::unique_ptr<SideStreams> s;
+    {
+        std::lock_guard<std::mutex> lk(g_side_mu);
+        for (auto it = g_side_free.begin(); it != g_side_free.end(); ++it)
+            if ((*it)->device == dev) {
+                s = std::move(*it);
+                g_side_free.erase(it);
+                break;
+            }
+    }
+    if (!s) {
+        s = std::make_unique<SideStreams>();
+        s->device = dev;
+    }
+    bool ok = s->fork || hipEventCreateWithFlags(&s->fork, hipEventDisableTiming) == hipSuccess;
+    while (ok && s->n < n) {
+        hipStream_t& st = s->stream[s->n];
+        hipEvent_t& ev = s->joined[s->n];
+        ok = (st || hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess) &&
+             (ev || hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess);
+        if (ok) ++s->n;
+    }
+    if (ok) return s;
+    std::lock_guard<std::mutex> lk(g_side_mu);
+    g_side_free.push_back(std::move(s));
+    return nullptr;
+}
 
 struct Plan {
     std::vector<uintptr_t> sig;
@@ -147,39 +197,47 @@ struct Plan {
     char* dbuf = nullptr;
     size_t dbytes = 0;
     std::vector<ClassPlan> classes;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    // recorded after every launch of the graph: an evicted plan is destroyed
-    // only once its last launch has finished (the launch may still be queued
-    // on another thread's stream when the plan leaves the cache)
+    std::unique_ptr<SideStreams> side;  // null: one class, or none to be had
+    // recorded after every launch: an evicted plan is destroyed only once its
+    // last launch has finished (it may still be queued on another thread's
+    // stream when the plan leaves the cache)
     hipEvent_t done = nullptr;
+    bool captured = false;  // a graph of the caller's holds launches of it
     ~Plan()
     {
         if (done) {
             (void)hipEventSynchronize(done);
             (void)hipEventDestroy(done);
         }
-        if (exec) (void)hipGraphExecDestroy(exec);
-        if (graph) (void)hipGraphDestroy(graph);
         if (dbuf) (void)hipFree(dbuf);
+        if (side) {
+            std::lock_guard<std::mutex> lk(g_side_mu);
+            g_side_free.push_back(std::move(side));
+        }
     }
 };
 
 // Plan cache, least recently used first.  Plans are shared: a caller holds
-// its plan until its graph launch has been enqueued, so a plan evicted by
-// another thread meanwhile stays alive until then (the graph itself may still
-// be running when the last holder lets go; hipFree of the plan's buffer waits
-// for it).
+// its plan until its launches have been enqueued, so a plan evicted by
+// another thread meanwhile stays alive until then (they may still be running
+// when the last holder lets go; ~Plan waits for them).  Plans whose
+// launches were captured are held in g_captured as well: the caller's graph
+// reads the plan's buffer as long as it is replayed.
 std::mutex g_plan_mu;
-std::vector<std::shared_ptr<Plan>> g_plans;
+std::vector<std::shared_ptr<Plan>> g_plans, g_captured;
 constexpr size_t kMaxPlans = 16;
 
 // Batched calls from several threads run one at a time inside the library:
-// planning, graph instantiation, launch and the destruction of evicted plans
-// are serialised (a two-thread test that fills the cache past its capacity
-// crashed inside this call with them running concurrently; the library's own
-// shared state is locked, so the HIP graph calls are the suspects).  The
+// planning, launch and the destruction of evicted plans are serialised.  The
 // enqueued work itself still runs concurrently on the callers' streams.
+//
+// The launches were the parallel nodes of one hipGraph per plan once.  The host
+// process then ended in a segfault inside the batched call three times, with no
+// GPU fault: twice with two threads that evicted each other's plans, once with
+// one thread at the 24th or 25th plan of its process.  No mistake was found in
+// this file's own code (built with the address sanitizer against a stub of the
+// runtime it makes 69 plans and evicts 50 without a finding), which leaves the
+// graph calls -- instantiate, launch, destroy -- as suspects: they are out.
 std::mutex g_batch_mu;
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -312,6 +370,9 @@ hipError_t upload_class(const std::vector<Triple>& tr, ClassPlan& cp, char* base
             e = hipMemcpy(base + cp.off_wi + off * sizeof(int32_t), f->d_wi,
                           n3 * sizeof(int32_t), hipMemcpyDeviceToDevice);
     }
+    // (copies on the device need not have ended when they return, and the class
+    // may run on a stream that does not wait for the null stream)
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     cp.nitems = (uint32_t)items.size();
     cp.args.vols = reinterpret_cast<const VolDesc*>(base + cp.off_desc);
     cp.args.items = reinterpret_cast<const WorkItem*>(base + cp.off_items);
@@ -327,6 +388,39 @@ hipError_t launch_class(const ClassPlan& cp, hipStream_t s)
     BatchArgs a = cp.args;
     void* params[] = {&a};
     return hipLaunchKernel(cp.func, dim3(cp.grid), dim3(256), params, 0, s);
+}
+
+// All classes of a plan, side by side on its side streams (one class: on the
+// caller's stream).  Up to three leave the caller's lane empty, so that they start
+// together: the class there runs ahead of the others by the fork, and whichever it was
+// some batch became slower (256 uint8 volumes of 16 to 96, k = 3, 5, 7: with 3,
+// 5 or 7 there 258, 238 and 273 us, with none 243; 64 float32 of 16 to 64: 124,
+// 113 and 107, with none 115; 16 uint16 of 8 to 48: 86, 100 and 92, with none
+// 86).  One after another on the caller's stream the last three sets take 287,
+// 141 and 115 us, as nodes of one graph they took 234, 114 and 88.
+hipError_t launch_plan(const Plan& p, hipStream_t s)
+{
+    if (!p.side) {
+        hipError_t e = hipSuccess;
+        for (size_t i = 0; i < p.classes.size() && e == hipSuccess; ++i)
+            e = launch_class(p.classes[i], s);
+        return e;
+    }
+    SideStreams& sd = *p.side;
+    const size_t lanes = std::min(p.classes.size(), sd.n);
+    hipError_t e = hipEventRecord(sd.fork, s);
+    size_t forked = 0;
+    for (; forked < lanes && e == hipSuccess; ++forked)
+        e = hipStreamWaitEvent(sd.stream[forked], sd.fork, 0);
+    for (size_t i = 0; i < p.classes.size() && e == hipSuccess; ++i)
+        e = launch_class(p.classes[i], p.classes[i].lane < lanes ? sd.stream[p.classes[i].lane] : s);
+    // joined whatever failed: s must not run ahead of what was launched
+    for (size_t l = 0; l < forked; ++l) {
+        hipError_t j = hipEventRecord(sd.joined[l], sd.stream[l]);
+        if (j == hipSuccess) j = hipStreamWaitEvent(s, sd.joined[l], 0);
+        if (e == hipSuccess) e = j;
+    }
+    return e;
 }
 
 // Time one class alone at a given slab depth (two launches on the caller's
@@ -365,6 +459,37 @@ float time_class(const std::vector<Triple>& tr, ClassPlan& cp, char* base, int t
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     return ms;
+}
+
+// Lanes of a plan's classes: a side stream each, or, where there are more classes
+// than those, the side streams and the caller's shared out: the longest class first,
+// each to the lane that is free soonest; a class takes some 40 us however small it is (a slab's chain of
+// planes), as long as 8e8 taps.  (9 classes of 24 volumes of 16 to 64, and of 96
+// of 32 to 128: 141 and 313 us, as nodes of one graph 143 and 310; by taps alone 154
+// and 315, dealt out in turn 132 and 334, to 3 lanes 181 and 344.)
+void assign_lanes(const std::vector<Triple>& tr, Plan& plan)
+{
+    if (plan.classes.size() <= plan.side->n) {
+        for (size_t i = 0; i < plan.classes.size(); ++i) plan.classes[i].lane = i;
+        return;
+    }
+    std::vector<std::pair<double, ClassPlan*>> order;
+    for (auto& cp : plan.classes) {
+        double taps = 8e8;
+        for (int idx : cp.members) {
+            const FilterJob& j = tr[idx].j;
+            taps += (double)j.X * j.Y * j.Z * j.k * j.k * j.k;
+        }
+        order.push_back({taps, &cp});
+    }
+    std::stable_sort(order.begin(), order.end(),
+                     [](const auto& a, const auto& b) { return a.first > b.first; });
+    std::vector<double> load(plan.side->n + 1, 0.0);
+    for (auto& o : order) {
+        const size_t l = std::min_element(load.begin(), load.end()) - load.begin();
+        load[l] += o.first;
+        o.second->lane = l;
+    }
 }
 
 vktError build_plan(const std::vector<Triple>& tr, std::vector<uintptr_t>&& sig, bool tune,
@@ -467,23 +592,11 @@ vktError build_plan(const std::vector<Triple>& tr, std::vector<uintptr_t>&& sig,
         if (cp.grid > cp.nitems) cp.grid = cp.nitems > 0 ? cp.nitems : 1;
     }
 
-    // one graph: the class kernels as independent (parallel) kernel nodes
-    e = hipGraphCreate(&plan->graph, 0);
-    for (auto& cp : plan->classes) {
-        if (e != hipSuccess) break;
-        hipKernelNodeParams p{};
-        void* params[] = {&cp.args};
-        p.func = const_cast<void*>(cp.func);
-        p.gridDim = dim3(cp.grid);
-        p.blockDim = dim3(256);
-        p.sharedMemBytes = 0;
-        p.kernelParams = params;
-        p.extra = nullptr;
-        hipGraphNode_t node;
-        e = hipGraphAddKernelNode(&node, plan->graph, nullptr, 0, &p);
-    }
-    if (e == hipSuccess) e = hipGraphInstantiate(&plan->exec, plan->graph, nullptr, nullptr, 0);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&plan->done, hipEventDisableTiming);
+    if (plan->classes.size() > 1)
+        plan->side = take_side_streams(plan->device,
+                                       std::min(plan->classes.size(), kSideStreams));
+    if (plan->side) assign_lanes(tr, *plan);
+    e = hipEventCreateWithFlags(&plan->done, hipEventDisableTiming);
     if (e != hipSuccess) return from_hip(e);
 
     out = plan;
@@ -757,8 +870,20 @@ vktError vktApplyFilterBatched(int32_t n, const vktStructuredVolume* dst,
         const vktError e = build_plan(tr, std::move(sig), thread_autotune(), stream, plan);
         if (e != vktNoError) return e;
     }
-    hipError_t e = hipGraphLaunch(plan->exec, stream);
-    if (e == hipSuccess) e = hipEventRecord(plan->done, stream);
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
+        (void)hipGetLastError();  // (the legacy stream, while another one is captured)
+        cap = hipStreamCaptureStatusNone;
+    }
+    hipError_t e = launch_plan(*plan, stream);
+    if (cap != hipStreamCaptureStatusNone) {
+        // (recorded, not run: nothing to wait for when the plan is evicted, but
+        // the caller's graph needs its buffer from now on)
+        if (!plan->captured) g_captured.push_back(plan);
+        plan->captured = true;
+    } else if (e == hipSuccess) {
+        e = hipEventRecord(plan->done, stream);
+    }
     return from_hip(e);
 }
 

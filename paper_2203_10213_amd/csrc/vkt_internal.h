@@ -252,9 +252,9 @@ const void* mfma_batched_kernel_s32(vktDataFormat f, int k, bool six_products, i
 ClassGeom mfma_geom_s16(vktDataFormat f, int k, bool six_products, int variant = 0);
 ClassGeom mfma_geom_s32(vktDataFormat f, int k, bool six_products, int variant = 0);
 
-// Batched persistent kernels: the kernel function of a class (for launches
-// and graph kernel nodes, taking one BatchArgs by value), its geometry, and
-// the workgroup count that fills the device once.
+// Batched persistent kernels: the kernel function of a class (taking
+// one BatchArgs by value), its geometry, and the workgroup count that fills the
+// device once.
 // Tile-height variants of every batched class: 0 = the default tile, 1 = a
 // tile half (matrix-core 32x32 tiles: twice) as tall; the autotuner times both.
 constexpr int kTileVariants = 2;
