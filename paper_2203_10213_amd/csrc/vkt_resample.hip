@@ -292,7 +292,7 @@ __global__ __launch_bounds__(kNT) void resample_kernel(const T* __restrict__ src
         }
     };
     T* out = dst + zb * oplane + (int64_t)y * Xo + x;
-    const bool whole = x + kXV <= Xo;
+    const bool whole = x <= Xo - kXV;  // (x + kXV may be 2^31)
     int have0 = -1, have1 = -1;  // source planes whose values are at hand
     float v0[kXV] = {}, v1[kXV] = {};
     for (int i = 0; i < nz; ++i, out += oplane) {
