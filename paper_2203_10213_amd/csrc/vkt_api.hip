@@ -422,8 +422,8 @@ VolDesc make_desc(const FilterJob& j, int tz, ClassGeom g)
     a.rx1 = j.roi[3];
     a.ry1 = j.roi[4];
     a.rz1 = j.roi[5];
-    a.tiles_x = (a.rx1 - a.rx0 + g.tx - 1) / g.tx;
-    a.tiles_y = (a.ry1 - a.ry0 + g.ty - 1) / g.ty;
+    a.tiles_x = tiles_along(a.rx1 - a.rx0, g.tx);
+    a.tiles_y = tiles_along(a.ry1 - a.ry0, g.ty);
     a.woff = 0;
     if (j.fmt == vktDataFormatFloat32) a.epi = j.int_filter ? kEpiFloatDiv : kEpiFloat;
     else a.epi = j.int_filter ? kEpiIntDiv : kEpiRound;

@@ -312,7 +312,7 @@ int default_tz(const std::vector<Triple>& tr, const ClassPlan& cp, const ClassGe
     int64_t n = 0;
     for (int idx : cp.members) {
         const FilterJob& j = tr[idx].j;
-        n += (int64_t)((j.X + g.tx - 1) / g.tx) * ((j.Y + g.ty - 1) / g.ty) *
+        n += (int64_t)tiles_along(j.X, g.tx) * tiles_along(j.Y, g.ty) *
              ((j.Z + kDeep - 1) / kDeep);
     }
     return n >= (int64_t)device_cus() ? kDeep : base;
@@ -523,7 +523,7 @@ vktError build_plan(const std::vector<Triple>& tr, std::vector<uintptr_t>&& sig,
             for (int idx : cp.members) {
                 const FilterJob& j = tr[idx].j;
                 const int tzmin = std::min(geom.tz_min, j.Z);
-                n += (size_t)((j.X + geom.tx - 1) / geom.tx) * ((j.Y + geom.ty - 1) / geom.ty) *
+                n += (size_t)tiles_along(j.X, geom.tx) * tiles_along(j.Y, geom.ty) *
                      ((j.Z + tzmin - 1) / tzmin);
             }
             nitems = std::max(nitems, n);

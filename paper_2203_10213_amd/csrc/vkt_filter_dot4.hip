@@ -192,7 +192,7 @@ __device__ void dot4_tile(const VolDesc& a, const uint32_t* __restrict__ wq, int
         srow[i] = gy < 0 ? kOutside : (uint32_t)gy * (uint32_t)a.X + (uint32_t)x0;
     }
     const uint32_t vlane = 4u * (uint32_t)lane;
-    const bool xin = x0 + 4 * lane + 4 <= a.X;               // dword inside the volume
+    const bool xin = 4 * lane + 4 <= a.X - x0;               // dword inside the volume
     uint32_t* const lrow = lds + wave * G::WD + 1 + lane;    // slot 0's LDS dword (buffer 0)
     uint32_t goff[NI + 1];  // [NI]: byte offset of the halo dword (face dwords: of the row)
     int32_t loff[NI + 1];   // [NI]: its LDS dword
@@ -203,7 +203,7 @@ __device__ void dot4_tile(const VolDesc& a, const uint32_t* __restrict__ wq, int
         const int hy = t / 2, right = t % 2;
         const bool live = t < 2 * G::HY;
         const int gy = live ? addr_map((int64_t)y0 - R + hy, a.Y, a.mode) : -1;
-        const int xr = min(x0 + kTX, a.X);  // first cell right of the staged part
+        const int xr = x0 + min(kTX, a.X - x0);  // first cell right of the staged part
         const int xb = right ? xr : x0 - 4;
         face = gy >= 0 && (right ? xr == a.X : x0 == 0);  // rows outside read zero whole
         fside = right;
@@ -275,8 +275,8 @@ __device__ void dot4_tile(const VolDesc& a, const uint32_t* __restrict__ wq, int
     if (P > 1) gather(zi_beg + 1);
     __syncthreads();
 
-    const int ox = x0 + 4 * lane;
-    const bool x_ok = ox < a.rx1;  // rx1 is a multiple of 4
+    const uint32_t ox = (uint32_t)x0 + vlane;
+    const bool x_ok = 4 * lane < a.rx1 - x0;  // rx1 is a multiple of 4
     const float inv_D = a.inv_D, bias = a.bias;
 
     // input plane p of the slab at ring position U = p mod k
@@ -513,7 +513,7 @@ hipError_t launch_r1(const FilterJob& j, hipStream_t s)
 {
     const ClassGeom g{kTX, kWaves * r1_rows(K), 1};
     const int RX = j.roi[3] - j.roi[0], RY = j.roi[4] - j.roi[1], RZ = j.roi[5] - j.roi[2];
-    const int64_t ntiles = (int64_t)((RX + g.tx - 1) / g.tx) * ((RY + g.ty - 1) / g.ty);
+    const int64_t ntiles = (int64_t)tiles_along(RX, g.tx) * tiles_along(RY, g.ty);
     const void* fn = (const void*)&filter_dot4_r1_kernel<K, SG, MODE>;
     const int tz = plan_tz(ntiles, RZ, K, 1, 128, resident_wgs(fn), K);
     const VolDesc a = make_desc(j, tz, g);
@@ -544,7 +544,7 @@ hipError_t launch_k(const FilterJob& j, hipStream_t s)
     const ClassGeom g = dot4_geom(K);
     // the output region's tiles and z extent (the whole volume unless a range)
     const int RX = j.roi[3] - j.roi[0], RY = j.roi[4] - j.roi[1], RZ = j.roi[5] - j.roi[2];
-    const int64_t ntiles = (int64_t)((RX + g.tx - 1) / g.tx) * ((RY + g.ty - 1) / g.ty);
+    const int64_t ntiles = (int64_t)tiles_along(RX, g.tx) * tiles_along(RY, g.ty);
     // tz = 1 mod k: the slab's tz + k - 1 input planes are whole ring turns
     const void* fn = (const void*)&filter_dot4_kernel<K, SG>;
     const int tz = plan_tz(ntiles, RZ, K, 1, 128, resident_wgs(fn), K);

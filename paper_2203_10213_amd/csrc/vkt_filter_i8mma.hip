@@ -357,7 +357,7 @@ hipError_t launch_filter_i8mma(const FilterJob& j, hipStream_t s)
     const ClassGeom g = i8mma_geom();
     const int RX = j.roi[3] - j.roi[0], RY = j.roi[4] - j.roi[1], RZ = j.roi[5] - j.roi[2];
     if (RX % 4 != 0 || j.roi[0] % 4 != 0 || j.X % 4 != 0) return hipErrorInvalidValue;
-    const int64_t ntiles = (int64_t)((RX + g.tx - 1) / g.tx) * ((RY + g.ty - 1) / g.ty);
+    const int64_t ntiles = (int64_t)tiles_along(RX, g.tx) * tiles_along(RY, g.ty);
     // tz = 1 mod 3: the slab's tz + 2 input planes are whole ring turns
     const void* fn = (const void*)&filter_i8mma_kernel;
     const int tz = plan_tz(ntiles, RZ, 3, 1, 128, resident_wgs(fn), 3);

@@ -253,11 +253,12 @@ __device__ void mfma_tile(const VolDesc& a, const float* __restrict__ w, int til
     constexpr int BY = C::BY, CPL = C::CPL;
     float* const blk = epi + wave * C::WX * BY;
     const int lrow = lane % BY, lpart = lane / BY;
-    const int xw = x0 + C::WX * wave + CPL * lpart, yl = y0 + lrow;
+    const int xt = C::WX * wave + CPL * lpart, yl = y0 + lrow;
+    const int nx = a.rx1 - x0 - xt;  // cells left in the row
     // rows past the volume's last row fall beyond the plane: dropped
     const uint32_t ooff =
-        yl < a.ry1 ? ((uint32_t)yl * (uint32_t)a.X + (uint32_t)xw) * (uint32_t)sizeof(T) : kOutside;
-    const bool vec_row = xw + CPL <= a.rx1;  // (buffer stores take any cell alignment)
+        yl < a.ry1 ? ((uint32_t)yl * (uint32_t)a.X + (uint32_t)x0 + (uint32_t)xt) * (uint32_t)sizeof(T) : kOutside;
+    const bool vec_row = nx >= CPL;  // (buffer stores take any cell alignment)
 
     acc_t acc[C::MTW];
 #pragma unroll
@@ -384,7 +385,7 @@ __device__ void mfma_tile(const VolDesc& a, const float* __restrict__ w, int til
             const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
                 static_cast<char*>(a.dst) + (int64_t)zo * plane_bytes, (short)0, plane_bytes,
                 (int)kRsrcWord3);
-            store_row<T, CPL>(rd, ooff, v, vec_row, a.rx1 - xw, a.unscale);
+            store_row<T, CPL>(rd, ooff, v, vec_row, nx, a.unscale);
             asm volatile("" ::: "memory");
         }
         // ---- advance the ring
@@ -487,7 +488,7 @@ hipError_t launch_cfg(const FilterJob& j, hipStream_t s)
     const ClassGeom g = geom_of<C>();
     // the output region's tiles and z extent (the whole volume unless a range)
     const int RX = j.roi[3] - j.roi[0], RY = j.roi[4] - j.roi[1], RZ = j.roi[5] - j.roi[2];
-    const int64_t ntiles = (int64_t)((RX + g.tx - 1) / g.tx) * ((RY + g.ty - 1) / g.ty);
+    const int64_t ntiles = (int64_t)tiles_along(RX, g.tx) * tiles_along(RY, g.ty);
     // Volumes that do not make two workgroups per CU even with one-plane slabs
     // take the 16x16 tile of one row block: twice the workgroups, half the step
     // of each, two-column strips for k = 5 (64^3 uint8, uint16, float32 5^3 8.4,

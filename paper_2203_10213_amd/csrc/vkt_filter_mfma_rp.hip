@@ -196,11 +196,12 @@ __device__ void rp_tile(const VolDesc& a, const float* __restrict__ w, int tile,
     constexpr int CP = C::TX / 4;
     typedef float evec __attribute__((ext_vector_type(C::EV)));
     const int srow = t / 4, scol = CP * (t % 4);
-    const int ys = y0 + srow, xst = x0 + scol;
+    const int ys = y0 + srow, nx = a.rx1 - x0 - scol;  // nx: cells left in the row
     // rows past the region's last row fall beyond the plane: dropped
     const uint32_t ooff =
-        ys < a.ry1 ? ((uint32_t)ys * (uint32_t)a.X + (uint32_t)xst) * (uint32_t)sizeof(T) : kOutside;
-    const bool vec_row = xst + CP <= a.rx1;  // (buffer stores take any cell alignment)
+        ys < a.ry1 ? ((uint32_t)ys * (uint32_t)a.X + (uint32_t)x0 + (uint32_t)scol) * (uint32_t)sizeof(T)
+                   : kOutside;
+    const bool vec_row = nx >= CP;  // (buffer stores take any cell alignment)
 
     f32x16 acc[C::WS];
 #pragma unroll
@@ -330,7 +331,7 @@ __device__ void rp_tile(const VolDesc& a, const float* __restrict__ w, int tile,
             const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
                 static_cast<char*>(a.dst) + (int64_t)zo * plane_bytes, (short)0, plane_bytes,
                 (int)kRsrcWord3);
-            store_row<T, CP>(rd, ooff, v, vec_row, a.rx1 - xst, a.unscale);
+            store_row<T, CP>(rd, ooff, v, vec_row, nx, a.unscale);
         }
         cur ^= 1;
     };
@@ -410,7 +411,7 @@ hipError_t rp_launch(const FilterJob& j, hipStream_t s)
     g.ty = C::TY;
     g.tz_min = 1;
     const int RX = j.roi[3] - j.roi[0], RY = j.roi[4] - j.roi[1], RZ = j.roi[5] - j.roi[2];
-    const int64_t ntiles = (int64_t)((RX + g.tx - 1) / g.tx) * ((RY + g.ty - 1) / g.ty);
+    const int64_t ntiles = (int64_t)tiles_along(RX, g.tx) * tiles_along(RY, g.ty);
     const void* fn = (const void*)&filter_mfma_rp_kernel<C>;
     // Slots of the plan: two workgroups per CU keep the matrix cores busy except
     // for uint8 (2 products); planned for the third that fits, 1024^3 float32

@@ -181,13 +181,14 @@ __device__ __attribute__((always_inline)) inline void sep_tile(
     if (zi_beg + 1 < zi_end) in.gather(a, zi_beg + 1);
     __syncthreads();
 
-    const int ox = x0 + kVX * tx, oy = y0 + kVY * ty;
-    const bool vec = ox + kVX <= a.rx1;
+    const int nx = a.rx1 - x0 - kVX * tx, oy = y0 + kVY * ty;  // nx: cells left in the row
+    const uint32_t ox = (uint32_t)x0 + (uint32_t)(kVX * tx);
+    const bool vec = nx >= kVX;
     uint32_t ooff[kVY];  // this thread's output rows (past the region: dropped)
 #pragma unroll
     for (int vy = 0; vy < kVY; ++vy)
         ooff[vy] = oy + vy < a.ry1
-                       ? ((uint32_t)(oy + vy) * (uint32_t)a.X + (uint32_t)ox) * (uint32_t)sizeof(T)
+                       ? ((uint32_t)(oy + vy) * (uint32_t)a.X + ox) * (uint32_t)sizeof(T)
                        : kOutside;
 
     auto step = [&](int zi, auto U) __attribute__((always_inline)) {
@@ -273,7 +274,7 @@ __device__ __attribute__((always_inline)) inline void sep_tile(
                 T r4[kVX];
 #pragma unroll
                 for (int vx = 0; vx < kVX; ++vx) r4[vx] = finish<T>(acc[old][vy][vx], a);
-                store4<T>(d, ooff[vy], r4, vec, a.rx1 - ox);
+                store4<T>(d, ooff[vy], r4, vec, nx);
             }
         }
     };
@@ -301,7 +302,7 @@ hipError_t launch_k(const FilterJob& j, hipStream_t s)
 {
     const ClassGeom g{kTX, kTY, 4 > 2 * K ? 4 : 2 * K};
     const int RX = j.roi[3] - j.roi[0], RY = j.roi[4] - j.roi[1], RZ = j.roi[5] - j.roi[2];
-    const int64_t ntiles = (int64_t)((RX + g.tx - 1) / g.tx) * ((RY + g.ty - 1) / g.ty);
+    const int64_t ntiles = (int64_t)tiles_along(RX, g.tx) * tiles_along(RY, g.ty);
     const void* fn = (const void*)&filter_sep_kernel<T, K, IACC>;
     const int tz = plan_tz(ntiles, RZ, K, 1, 128, resident_wgs(fn), 1);
     const VolDesc a = make_desc(j, tz, g);

@@ -244,13 +244,14 @@ __device__ void valu_tile(const VolDesc& a, const typename AccT<IACC>::type* __r
     if (zi_beg + 1 < zi_end) in.gather(a, zi_beg + 1);
     __syncthreads();
 
-    const int ox = x0 + kVX * tx, oy = y0 + kVY * ty;
-    const bool vec = ox + kVX <= a.rx1;
+    const int nx = a.rx1 - x0 - kVX * tx, oy = y0 + kVY * ty;  // nx: cells left in the row
+    const uint32_t ox = (uint32_t)x0 + (uint32_t)(kVX * tx);
+    const bool vec = nx >= kVX;
     uint32_t ooff[kVY];  // this thread's output rows (past the region: dropped)
 #pragma unroll
     for (int vy = 0; vy < kVY; ++vy)
         ooff[vy] = oy + vy < a.ry1
-                       ? ((uint32_t)(oy + vy) * (uint32_t)a.X + (uint32_t)ox) * (uint32_t)sizeof(T)
+                       ? ((uint32_t)(oy + vy) * (uint32_t)a.X + ox) * (uint32_t)sizeof(T)
                        : kOutside;
     // one input plane; ring slot of filter plane c: c (k >= 5, the ring moves),
     // (c - U) mod k at plane U mod k (k <= 3, the loop unrolled by k)
@@ -364,7 +365,7 @@ __device__ void valu_tile(const VolDesc& a, const typename AccT<IACC>::type* __r
                 T r4[kVX];
 #pragma unroll
                 for (int vx = 0; vx < kVX; ++vx) r4[vx] = finish<T>(acc[done][vy][vx], a);
-                store4<T>(d, ooff[vy], r4, vec, a.rx1 - ox);
+                store4<T>(d, ooff[vy], r4, vec, nx);
             }
         }
         // ---- advance the ring: slot c now belongs to output plane zi+1-c+r
@@ -456,10 +457,10 @@ __global__ __launch_bounds__(kNT) void filter_direct_kernel(
 {
     using Acc = typename AccT<IACC>::type;
     constexpr int R = (K - 1) / 2;
-    const int x = a.rx0 + (int)blockIdx.x * kDirectBX + (int)threadIdx.x;
-    const int y = a.ry0 + (int)blockIdx.y * kDirectBY + (int)threadIdx.y;
-    const int z = a.rz0 + (int)blockIdx.z;
-    if (x >= a.rx1 || y >= a.ry1) return;
+    const int xr = (int)blockIdx.x * kDirectBX + (int)threadIdx.x;
+    const int yr = (int)blockIdx.y * kDirectBY + (int)threadIdx.y;
+    if (xr >= a.rx1 - a.rx0 || yr >= a.ry1 - a.ry0) return;
+    const int x = a.rx0 + xr, y = a.ry0 + yr, z = a.rz0 + (int)blockIdx.z;
     int xs[K], ys[K], zs[K];  // coordinates through the address mode; -1: zero
 #pragma unroll
     for (int t = 0; t < K; ++t) {
@@ -514,7 +515,7 @@ hipError_t launch_k(const FilterJob& j, hipStream_t s)
     }
     // the output region's tiles and z extent (the whole volume unless a range)
     const int RX = j.roi[3] - j.roi[0], RY = j.roi[4] - j.roi[1], RZ = j.roi[5] - j.roi[2];
-    const int64_t ntiles = (int64_t)((RX + g.tx - 1) / g.tx) * ((RY + g.ty - 1) / g.ty);
+    const int64_t ntiles = (int64_t)tiles_along(RX, g.tx) * tiles_along(RY, g.ty);
     const void* fn = (const void*)&filter_valu_kernel<T, K, IACC>;
     // Slots of the plan: for k <= 3, bound by HBM, at most five workgroups per
     // CU (six measured slower, with thinner slabs and more halo planes: 512^3

@@ -203,6 +203,9 @@ struct ClassGeom {
     int tz_min;              // smallest useful slab depth
 };
 
+// Tiles of t cells that cover n (n as large as 2^31 - 1).
+inline int32_t tiles_along(int32_t n, int32_t t) { return (int32_t)(((int64_t)n + t - 1) / t); }
+
 // Kernel launchers (return the launch status).
 hipError_t launch_fill(void* dst, int cell_bytes, int64_t n_cells,
                        uint32_t raw_bits, hipStream_t s);

@@ -130,7 +130,10 @@ struct PlaneStage {
     {
         const int xl = x0 - R;
         const int32_t plane_cells = a.X * a.Y;
-        face = xl < 0 || xl + COLS > a.X;
+        // staged columns up to the volume's right face, at most one quad past the
+        // tile (X may be as large as 2^31 - 1: no sum of it and a width)
+        const int cols = (int)min((int64_t)a.X - xl, (int64_t)COLS + 4);
+        face = xl < 0 || cols < COLS;
         inner = 0;
         if constexpr (LINEAR) {
             qpos[0] = 4 * t;
@@ -142,13 +145,12 @@ struct PlaneStage {
             const int hy = e / QR, hx = 4 * (e % QR);
             if constexpr (!LINEAR) qpos[i] = Pos::at(hy, hx);
             const int gy = addr_map((int64_t)y0 - R + hy, a.Y, a.mode);
-            const int xs = xl + hx;
             // (a face quad's load stays inside the plane; it is not staged; a
             // row outside the volume under border mode reads 0; in planes of
             // fewer than 4 cells every quad is a face quad)
-            const int32_t cell = min(max(gy, 0) * a.X + max(xs, 0), plane_cells - 4);
+            const int32_t cell = min(max(gy, 0) * a.X + max(xl + min(hx, cols - 1), 0), plane_cells - 4);
             goff[i] = gy < 0 || cell < 0 ? kOutside : (uint32_t)cell * (uint32_t)sizeof(T);
-            if (xs >= 0 && xs + 3 < a.X) inner |= 1u << i;
+            if (hx >= -xl && hx + 3 < cols) inner |= 1u << i;
         }
 #pragma unroll
         for (int i = 0; i < NF; ++i) fpos[i] = -1;
@@ -156,8 +158,8 @@ struct PlaneStage {
             // quads with columns before cell 0, then those from the one that
             // holds column X to the one that holds column X + R - 1
             const int nl = xl < 0 ? min(QR, (-xl + 3) / 4) : 0;
-            const int q1 = (a.X - xl) / 4, qr0 = max(nl, q1);
-            const int ql = min(QR - 1, max(q1, (a.X + R - 1 - xl) / 4));
+            const int q1 = cols / 4, qr0 = max(nl, q1);
+            const int ql = min(QR - 1, max(q1, (cols + R - 1) / 4));
             const int nf = nl + max(0, ql - qr0 + 1);
 #pragma unroll
             for (int i = 0; i < NF; ++i) {

@@ -48,3 +48,69 @@ def test_resample_to_a_row_that_ends_at_2_31(n):
         want = np.floor(s[a] * (1 - f) + s[b] * f + 0.5)
         got = dst[i0:i0 + 300].cpu().numpy().astype(np.float64)
         assert np.abs(got - want).max() <= 1, i0
+
+
+def _weights(k):
+    w = np.abs(np.random.default_rng(k).standard_normal((k, k, k))) + 0.1
+    return (w / w.sum()).astype(np.float32)
+
+
+def _box(k):
+    return np.ones((k, k, k), np.int32), k ** 3
+
+
+# (cells in the row, path, region's width, filter, precision): the direct and the
+# tiled vector kernel (k = 3, 5 in FP32), the exact passes, the 8-bit dot products
+# (dense and in passes; rows of whole dwords only), the 16x16, 32x32 and row-pair
+# matrix kernels
+CASES = [(END - 1, "direct", 1001, 3, "auto"), (END - 1, "float", 600001, 3, "auto"),
+         (END - 3, "float", 1001, 5, "fp32"), (END - 1, "box", 1001, 5, "auto"),
+         (END - 2, "box", 600002, 3, "auto"), (END - 4, "box", 1000, 5, "auto"),
+         (END - 4, "signed", 1000, 3, "auto"), (END - 1, "float", 1001, 5, "auto"),
+         (END - 6, "float", 30001, 7, "auto"), (END - 1, "float", 1001, 9, "auto"),
+         (END - 1, "pairs", 20001, 5, "auto")]
+
+
+@pytest.mark.parametrize("mode", ["clamp", "mirror"])
+@pytest.mark.parametrize("n,path,width,k,prec", CASES)
+def test_filter_region_at_the_end_of_a_long_row(n, path, width, k, prec, mode):
+    """The last `width` cells of the row, against the same cells of a volume that
+    holds only the row's end (the region starts at the same place of a tile, so
+    results are compared bit for bit)."""
+    import torch
+    from paper_2203_10213_amd import vkt
+    keep = width + 64
+    vkt.vktSetStream(torch.cuda.current_stream())
+    vkt.vktSetPrecision(prec)
+    rp = vkt.vktGetRowPairMinCells()
+    if path == "pairs":
+        vkt.vktSetRowPairMinCells(0)
+    buf_s, src = _guarded(torch, n)
+    buf_d, dst = _guarded(torch, n)
+    tail = torch.randint(0, 256, (1, 1, keep), dtype=torch.uint8, device="cuda",
+                         generator=torch.Generator(device="cuda").manual_seed(k))
+    src[n - keep:] = tail.view(-1)
+    want = torch.zeros_like(tail)
+    if path == "box":
+        f = vkt.vktFilterCreateInt(*_box(k))
+    elif path == "signed":
+        w = np.random.default_rng(1).integers(-3, 6, (k, k, k)).astype(np.int32)
+        f = vkt.vktFilterCreateInt(w, 40)
+    else:
+        f = vkt.vktFilterCreate(_weights(k))
+    hs, hd = (vkt.vktStructuredVolumeCreateFromDevicePtr((n, 1, 1), vkt.vktDataFormatUInt8,
+                                                         t.data_ptr()) for t in (src, dst))
+    ts, td = vkt.volume_from_tensor(tail), vkt.volume_from_tensor(want)
+    vkt.vktApplyFilterRange(hd, hs, f, (n - width, 0, 0), (n, 1, 1), mode)
+    vkt.vktApplyFilterRange(td, ts, f, (keep - width, 0, 0), (keep, 1, 1), mode)
+    torch.cuda.synchronize()
+    for h in (hs, hd, ts, td):
+        vkt.vktStructuredVolumeDestroy(h)
+    vkt.vktFilterDestroy(f)
+    vkt.vktSetRowPairMinCells(rp)
+    vkt.vktSetPrecision("auto")
+    vkt.vktSetStream(None)
+    assert _guards_hold(buf_s) and _guards_hold(buf_d)
+    assert torch.equal(dst[n - keep:], want.view(-1))
+    assert bool((want.view(-1)[keep - width:] > 0).any())
+    assert not bool(dst[:n - keep].any())
