@@ -457,17 +457,30 @@ __global__ __launch_bounds__(kNT) void filter_direct_kernel(
 {
     using Acc = typename AccT<IACC>::type;
     constexpr int R = (K - 1) / 2;
-    const int xr = (int)blockIdx.x * kDirectBX + (int)threadIdx.x;
-    const int yr = (int)blockIdx.y * kDirectBY + (int)threadIdx.y;
-    if (xr >= a.rx1 - a.rx0 || yr >= a.ry1 - a.ry0) return;
-    const int x = a.rx0 + xr, y = a.ry0 + yr, z = a.rz0 + (int)blockIdx.z;
+    // (unsigned: a workgroup may reach past 2^31 - 1)
+    const uint32_t xu = (uint32_t)a.rx0 + blockIdx.x * kDirectBX + threadIdx.x;
+    const uint32_t yu = (uint32_t)a.ry0 + blockIdx.y * kDirectBY + threadIdx.y;
+    if (xu >= (uint32_t)a.rx1 || yu >= (uint32_t)a.ry1) return;
+    const int x = (int)xu, y = (int)yu, z = a.rz0 + (int)blockIdx.z;
     int xs[K], ys[K], zs[K];  // coordinates through the address mode; -1: zero
-#pragma unroll
-    for (int t = 0; t < K; ++t) {
-        xs[t] = addr_map((int64_t)x + t - R, a.X, a.mode);
-        ys[t] = addr_map((int64_t)y + t - R, a.Y, a.mode);
-        zs[t] = addr_map((int64_t)z + t - R, a.Z, a.mode);
-    }
+    // with taps one cell to either side the address mode is a matter of two
+    // coordinates per axis, the same for all threads (addr_map for every tap was
+    // 135 branches a thread: 48x81x89 uint16 dense 3^3 7.67 us, now 6.88; 64^3
+    // float32 5.81, now 5.36)
+    static_assert(R <= 1, "one cell to either side");
+    auto taps = [&](int i, int n, int (&c)[K]) __attribute__((always_inline)) {
+        const bool wrap = a.mode == vktAddressModeWrap, border = a.mode == vktAddressModeBorder;
+        const int before = border ? -1 : wrap ? n - 1 : 0;     // what cell -1 reads
+        const int after = border ? -1 : wrap ? 0 : n - 1;      // what cell n reads
+        c[R] = i;
+        if constexpr (R == 1) {
+            c[0] = i > 0 ? i - 1 : before;
+            c[2] = i < n - 1 ? i + 1 : after;
+        }
+    };
+    taps(x, a.X, xs);
+    taps(y, a.Y, ys);
+    taps(z, a.Z, zs);
     const T* __restrict__ src = static_cast<const T*>(a.src);
     Acc acc = 0;
 #pragma unroll
