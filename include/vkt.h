@@ -214,7 +214,8 @@ vktError vktApplyFilterRange(vktStructuredVolume dst, vktStructuredVolume src,
  * plan of a batch size class times, per class, both tile heights of the class kernel at
  * candidate z-slab depths on the real data (this writes the outputs and
  * waits for the stream) and records the fastest tile and depth;
- * VKT_TUNE_CACHE=<file> keeps that table across processes.
+ * VKT_TUNE_CACHE=<file> keeps that table across processes; an entry names the
+ * tile that it was timed on and is ignored where this build's tile is another.
  * Errors: as vktApplyFilter for any pair; vktInvalidValue for n < 0, NULL
  * arrays or overlapping outputs; vktOutOfMemory for the plan buffer. */
 vktError vktApplyFilterBatched(int32_t n, const vktStructuredVolume* dst,

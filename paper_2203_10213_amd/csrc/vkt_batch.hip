@@ -106,10 +106,15 @@ void tune_load_locked()
     while (std::fgets(line, sizeof line, f)) {
         TuneKey k;
         TuneVal v{0, 0};
-        // fmt k path flag size_class tz [variant]
-        const int n = std::sscanf(line, "%d %d %d %d %d %d %d", &k.c.fmt, &k.c.k, &k.c.path,
-                                  &k.c.flag, &k.size_class, &v.tz, &v.variant);
-        if (n >= 6 && v.tz > 0 && v.variant >= 0 && v.variant < kTileVariants) g_tune[k] = v;
+        int tx = 0, ty = 0;
+        // fmt k path flag size_class tz variant tx ty: the entry and the tile that
+        // it was timed on.  Lines for another tile than the variant has now, or
+        // without one (older files), say nothing about these kernels.
+        const int n = std::sscanf(line, "%d %d %d %d %d %d %d %d %d", &k.c.fmt, &k.c.k, &k.c.path,
+                                  &k.c.flag, &k.size_class, &v.tz, &v.variant, &tx, &ty);
+        if (n < 9 || v.tz <= 0 || v.variant < 0 || v.variant >= kTileVariants) continue;
+        const ClassGeom g = class_geom(k.c, v.variant);
+        if (g.tx == tx && g.ty == ty) g_tune[k] = v;
     }
     std::fclose(f);
 }
@@ -120,9 +125,11 @@ void tune_store_locked()
     if (!path) return;
     FILE* f = std::fopen(path, "w");
     if (!f) return;
-    for (const auto& e : g_tune)
-        std::fprintf(f, "%d %d %d %d %d %d %d\n", e.first.c.fmt, e.first.c.k, e.first.c.path,
-                     e.first.c.flag, e.first.size_class, e.second.tz, e.second.variant);
+    for (const auto& e : g_tune) {
+        const ClassGeom g = class_geom(e.first.c, e.second.variant);
+        std::fprintf(f, "%d %d %d %d %d %d %d %d %d\n", e.first.c.fmt, e.first.c.k, e.first.c.path,
+                     e.first.c.flag, e.first.size_class, e.second.tz, e.second.variant, g.tx, g.ty);
+    }
     std::fclose(f);
 }
 
