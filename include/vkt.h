@@ -225,9 +225,9 @@ vktError vktApplyFilterBatched(int32_t n, const vktStructuredVolume* dst,
 /* Allocation-free batched form, for callers that cannot allocate device
  * memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc).  Same arguments, validation and results as
- * vktApplyFilterBatched -- the same class kernels, slab depths (the tuning
- * table's entry, else the default; this call never tunes) and summation
- * order -- but no plan, graph or device buffer is created: the batch's
+ * vktApplyFilterBatched -- the same class kernels, tiles and slab depths (the
+ * tuning table's entry, else the default; this call never tunes) and summation
+ * order -- but no plan or device buffer is created: the batch's
  * descriptors, work lists, work-queue counters and weight pools go to a
  * static device array of the library, 8 MiB per GPU, held by each GPU the
  * library runs on until the process ends.  Each call uploads that data
@@ -239,8 +239,11 @@ vktError vktApplyFilterBatched(int32_t n, const vktStructuredVolume* dst,
  * calls in order on one stream are safe.  The host waits only for the
  * previous call's upload to have been read.
  * Limit: the batch's descriptors (one per volume), work items (one per output
- * tile-slab of every volume) and weight pools must fit the 8 MiB array;
- * otherwise vktUnsupported is returned before anything is enqueued.
+ * tile-slab of every volume) and weight pools must fit the 8 MiB array.  Where
+ * they do not, the classes that have a taller tile take it, and slabs at least
+ * as deep as that tile's default (fewer items; the sums and their order are the
+ * same); if that does not fit either, vktUnsupported is returned before
+ * anything is enqueued.
  * Errors: as vktApplyFilterBatched, plus vktUnsupported for a batch beyond
  * the limit. */
 vktError vktApplyFilterBatchedNoAlloc(int32_t n, const vktStructuredVolume* dst,

@@ -748,12 +748,17 @@ vktError batched_no_alloc(const std::vector<Triple>& tr, hipStream_t stream)
             cp.members = g.second;
             const TuneVal tv = tuned(tune_key(tr, cp));
             cp.variant = tv.tz > 0 ? tv.variant : 0;
-            if (taller && class_geom(cp.key, 1 - cp.variant).ty > class_geom(cp.key, cp.variant).ty)
+            int tz = tv.tz;  // 0: none
+            if (taller && class_geom(cp.key, 1 - cp.variant).ty > class_geom(cp.key, cp.variant).ty) {
+                // (the table's depth was timed on the other tile; it stays where it
+                // is the deeper one, which makes fewer items)
                 cp.variant = 1 - cp.variant;
+                tz = std::max(tz, default_tz(tr, cp, class_geom(cp.key, cp.variant)));
+            }
             cp.func = class_kernel(cp.key, cp.variant);
             if (!cp.func) return 0;
             const ClassGeom geom = class_geom(cp.key, cp.variant);
-            cp.tz = std::max(tv.tz > 0 ? tv.tz : default_tz(tr, cp, geom), geom.tz_min);
+            cp.tz = std::max(tz > 0 ? tz : default_tz(tr, cp, geom), geom.tz_min);
             std::vector<float> wf;
             std::vector<int32_t> wi;
             class_arrays(tr, cp, descs[c], items[c], wf, wi);
