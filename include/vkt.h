@@ -66,6 +66,13 @@ typedef enum vktPrecision {
     vktPrecisionSplitBF16 = 2,   /* matrix cores, 3 bf16 products for Float32 */
     vktPrecisionSplitBF16x6 = 3  /* matrix cores, 6 bf16 products for Float32 */
 } vktPrecision;
+/* Float32 cells that are not finite (or round to infinity in bf16, above
+ * 3.38e38): an output whose filter reads one is not finite.  With FP32 (and in
+ * the rank-1 passes) no other output is touched.  The split precisions multiply
+ * such a cell by zero weights as well: outputs up to 7 columns and one row
+ * further from it than the filter reaches may become NaN, on its planes alone.
+ * Which of them do depends on where the region's tiles lie, so on the filter's
+ * size, the region and the tile that is chosen for it. */
 
 /* Axis of a volume: x (fastest in memory), y, z. */
 typedef enum vktAxis {
@@ -309,7 +316,7 @@ vktError vktBrickDecomposeGetBrickDims(vktStructuredVolume src, int32_t brickX,
 /* Write every brick: bricks[bx + numX*(by + numY*bz)] for all n =
  * numX*numY*numZ bricks, each a volume of src's format with exactly the
  * dims above (created by the caller, e.g. with vktStructuredVolumeCreate).
- * One launch per 128 bricks, no device allocation.  Errors: as above, and
+ * One launch per 512 bricks, no device allocation.  Errors: as above, and
  * vktInvalidValue when n differs from the brick count, a brick has the wrong
  * dims or format, a mode is out of range, or brick buffers overlap each
  * other or src. */
