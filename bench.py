@@ -512,8 +512,8 @@ def run_batched(args, vkt, torch):
     else:
         roof = {"bound": "mfma", "achieved": mfma_flops / t / 1e12, "peak": BF16_MFMA_PEAK_TF,
                 "unit": "TFLOP/s", "frac": mfma_flops / t / 1e12 / BF16_MFMA_PEAK_TF}
-    roof.update({"traffic": stored_profile("c4_batched_graph", "batched", "hbm_bytes_per_launch"),
-                 "kernel_case": "c4 batched graph (all classes, one launch)"})
+    roof.update({"traffic": stored_profile("c4_batched", "batched", "hbm_bytes_per_launch"),
+                 "kernel_case": "c4 batched call (all classes)"})
     cpu = None
     if not args.no_cpu_baseline:
         import oracle

@@ -343,9 +343,8 @@ vktError vktSetAutotune(int enable);
 
 /* Rank-1 fast path (opt-in, per thread; default: the VKT_SEPARABLE
  * environment variable, "1" enables).  (Integer rank-1 filters on integer
- * cells run in three exact passes without it, where that is faster: the same
- * sums, on the vector ALUs or as 8-bit dot products as before.)  A filter whose weights factor as
- * w[c][b][a] = t[c] v[b] u[a] -- exactly for integer filters; for float
+ * cells run in three exact passes without it, where that is faster, with the
+ * same sums.)  A filter whose weights factor as w[c][b][a] = t[c] v[b] u[a] -- exactly for integer filters; for float
  * filters every weight to within 2^-20 of itself (so the three passes stay
  * within about 2^-20 sum|w||s| of the dense sum, plus their own FP32
  * rounding) -- then runs as three one-dimensional
@@ -372,8 +371,9 @@ vktError vktGetInt8Matrix(int* enable);
  * VKT_ROW_PAIR_MIN_CELLS environment variable).  Matrix-core jobs with k = 5,
  * and float32 k = 7 with 3 products, whose output region (the whole volume,
  * or the ROI of a range call) has more than `cells` cells run on the 32x32x16
- * row-pair kernel; smaller ones run on 16x16x32 tiles, which measured faster
- * for batches of volumes up to 256^3.  Both compute the same split products;
+ * row-pair kernel; smaller ones run on 16x16x32 tiles.  (The default was set
+ * with earlier kernels; for k = 5 the row pairs are the faster ones from about
+ * 2^21 cells on today.)  Both compute the same split products;
  * the summation order differs, so float results may differ by rounding
  * (within the stated tolerances).  A batch chooses per volume exactly as the
  * single call would.  Errors: vktInvalidValue for cells < 0 or a NULL
@@ -400,7 +400,10 @@ typedef enum vktFilterPath {
 /* The path vktApplyFilter(dst, src, filter, mode) would take on the calling
  * thread now (its precision, separable and int8-matrix settings, and the
  * volumes' sizes and alignment), chosen by the same planning code as the
- * call itself; nothing is enqueued.  *products receives the number of
+ * call itself; nothing is enqueued.  Integer rank-1 filters on integer cells
+ * that run in three exact passes unasked report the path that the dense sum
+ * would take (vector FP32, or 8-bit dot products, which the passes then use
+ * along x): the sums are the same.  *products receives the number of
  * partial products per multiply-add on the split matrix path (uint8 cells 2,
  * uint16 4, Float32 3 or 6) and 1 on every other path.  products may be NULL.
  * Ownership: nothing is retained.  Errors: as vktApplyFilter, plus

@@ -549,13 +549,26 @@ vktError build_job(const vktStructuredVolume_* dst, const vktStructuredVolume_* 
     return vktNoError;
 }
 
-// k = 5, 7 run on 32x32x16 tiles over row pairs, except where the 16x16x32
-// kernel measured faster: uint8 / uint16 and 6-product float32 with k = 7 on
-// 512^3 volumes, and output regions of at most the thread's row-pair
-// threshold (default 2^24 cells: 256 uneven uint16 volumes of up to 256^3 in
-// one batch take 2.59 ms with the 16x16x32 kernel's 16-row tiles against
-// 2.81 ms with row pairs for k = 5).  Single and batched launches choose
-// alike, so a batch reproduces its volumes' single launches bit for bit.
+// k = 5, and 7 with 3-product float32, run on 32x32x16 tiles over row pairs where
+// the output region has more cells than the thread's threshold, else on 16x16x32
+// tiles.  (k = 7 with uint8, uint16 and 6-product float32 measured faster on
+// 16x16x32 tiles; there is no row-pair kernel for them.)  Single and batched
+// launches choose alike, so a batch reproduces its volumes' single launches bit
+// for bit.
+//
+// The default, 2^24 cells, was set with earlier kernels of both kinds (the row-pair
+// ones spilled in the batched form).  With the present ones the row pairs win for
+// k = 5 from about 2^21 cells on: us on 16x16x32 tiles and row pairs, n^3 volumes,
+//              n =  96          128          200          256
+//   uint8        10.8 / 12.0  13.9 / 13.2  29.1 / 22.4  44.6 / 29.1
+//   uint16       14.4 / 16.1  18.5 / 16.4  38.7 / 30.7  59.1 / 43.6
+//   float32 x6   19.0 / 21.2  24.3 / 22.5  49.7 / 44.4  76.9 / 65.7
+//   float32 x3   13.6 / 14.7  18.0 / 15.6  37.5 / 29.8  56.9 / 43.9
+//   x3, k = 7    16.0 / 17.9  20.7 / 21.3  40.8 / 42.3  66.9 / 61.3
+// and 256 uneven uint16 volumes of up to 256^3 in one batch take 2128 us with the
+// line at 2^24, 2086 at 2^22 and 2038 at 0.  The default is part of the interface
+// and decides which kernel's rounding a call gets, so it stays;
+// vktSetRowPairMinCells moves the line.
 bool mfma_row_pairs(const FilterJob& j, bool six_products)
 {
     const int64_t cells =

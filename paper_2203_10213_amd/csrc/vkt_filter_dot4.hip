@@ -492,16 +492,18 @@ void filter_dot4_batched_kernel(BatchArgs b)
     }
 }
 
-// Output rows per lane and waves per SIMD of the rank-1 kernels (3^3 with 8
-// rows: 75 us on 512^3, 18.0 on 256^3; with 4 rows 71 and 12.9).
-constexpr int r1_rows(int) { return 4; }
-constexpr int r1_waves(int k, int mode) { return k <= 3 ? 4 : mode == kPassPacked ? 4 : 2; }
+// Output rows per lane of the rank-1 kernels (3^3 with 8 rows: 75 us on 512^3,
+// 18.0 on 256^3; with 4 rows 71 and 12.9).
+constexpr int kR1Rows = 4;
+// Waves per SIMD: four where the sums fit 128 registers (3^3 71, packed 5^3 96 and
+// 7^3 117); sums of 32 bits take 153 and 189 for 5^3 and 7^3 and would spill.
+constexpr int r1_waves(int k, int mode) { return k <= 3 || mode == kPassPacked ? 4 : 2; }
 
 template <int K, bool SG, int MODE>
 __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(r1_waves(K, MODE))))
 void filter_dot4_r1_kernel(VolDesc a, R1Args r1, uint32_t nblocks)
 {
-    constexpr int VY = r1_rows(K);
+    constexpr int VY = kR1Rows;
     __shared__ __align__(16) uint32_t lds[2 * Geo4<K, VY>::PLANE_BUF];
     const uint32_t lid = xcd_remap(blockIdx.x, nblocks);
     const uint32_t ntiles = (uint32_t)a.tiles_x * (uint32_t)a.tiles_y;
@@ -511,7 +513,7 @@ void filter_dot4_r1_kernel(VolDesc a, R1Args r1, uint32_t nblocks)
 template <int K, bool SG, int MODE>
 hipError_t launch_r1(const FilterJob& j, hipStream_t s)
 {
-    const ClassGeom g{kTX, kWaves * r1_rows(K), 1};
+    const ClassGeom g{kTX, kWaves * kR1Rows, 1};
     const int RX = j.roi[3] - j.roi[0], RY = j.roi[4] - j.roi[1], RZ = j.roi[5] - j.roi[2];
     const int64_t ntiles = (int64_t)tiles_along(RX, g.tx) * tiles_along(RY, g.ty);
     const void* fn = (const void*)&filter_dot4_r1_kernel<K, SG, MODE>;

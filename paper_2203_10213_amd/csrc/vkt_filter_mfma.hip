@@ -26,7 +26,7 @@
 // slab) and the weights turn: a lane reads the weights of the next filter
 // plane from a table in LDS.  Moving them instead took 64 ds_bpermute a plane
 // and wave behind the last product and kept the weights in registers (11^3
-// uint16 224 registers, now 156; 1024^3 15.25 -> 14.85 ms, 400x380x360 13^3
+// uint16 224 registers, now 152; 1024^3 15.25 -> 14.85 ms, 400x380x360 13^3
 // 1.15 -> 1.06 ms, 200x190x181 float32 15^3 with 6 products 484 -> 429 us).
 //
 // The four x-strips a wave owns are adjacent, so one segment read per (row
@@ -92,7 +92,8 @@ struct Cfg {
     // float32 9^3 (no spills; with two-column strips 1024^3 12.45 -> 11.77 ms,
     // 512^3 1.66 -> 1.58 ms, bit-identical).  The other 32x32 kernels read each
     // group's segments just before its products: uint8 9^3 / 11^3 measured 1 %
-    // slower pipelined, float32 11^3 the same, and 6-product float32 spills.
+    // slower pipelined, float32 11^3 the same, and 6-product float32 spilled (all
+    // three measured with the weights in registers).
     static constexpr bool PIPE = SHAPE == 16 || std::is_same<T, uint16_t>::value ||
                                  (std::is_same<T, float>::value && PM != kF32x6 && K <= 9);
     static constexpr int SY_DEFAULT = SHAPE == 16 ? 2 : 1;
@@ -103,8 +104,11 @@ struct Cfg {
     // read 8 bytes (24-byte wave offsets) or 16 bytes at a time
     static constexpr int RD = WX % 8 == 0 ? 4 : 2;
     static constexpr int SEGD = ((NX * (WS - 1) + 8 + 1) / 2 + RD - 1) / RD * RD;
-    // staged columns, and the row pitch that spreads the segment reads of
-    // consecutive rows over the LDS banks (an odd number of reads)
+    // staged columns, and the row pitch: for 8-byte reads and for k = 7 an odd
+    // number of reads, which spreads the segment reads of consecutive rows over the
+    // LDS banks.  The other kernels with 16-byte reads keep 48 columns, 6 reads (11^3
+    // uint16: bank conflicts add 66 % to the LDS cycles, under products that keep the
+    // matrix cores 81 % busy)
     static constexpr int COLS = (3 * WX + (SHAPE == 16 ? 0 : 8) + 2 * SEGD + 7) / 8 * 8;
     static constexpr int PITCH = RD == 2 ? (COLS % 8 == 0 ? COLS + 4 : COLS) : COLS;
     static_assert(TX + K - 1 <= COLS && PITCH * 2 % (4 * RD) == 0, "staged columns");
@@ -118,17 +122,16 @@ struct Cfg {
     // output block of a wave: WX x BY cells, CPL of a row per lane
     static constexpr int BY = SY * M::MT, CPL = WX * BY / 64;
     static constexpr int MTW = WS * SY;                             // M tiles per wave
-    // waves per SIMD the single-volume kernel is compiled for: 16x16 tiles
-    // with uint8 or 3-product float32 operands fit 128 registers (four
-    // waves) without spills; uint16 and 6-product float32 would spill there
-    // and keep three; 32x32 tiles take what they need (one or two), except
-    // the one-block kernels, held to two waves (196-256 registers; 15^3
-    // uint16 and 11^3 six-product float32 spill 14 and 15, and measured
-    // faster or no slower)
+    // waves per SIMD that the single-volume kernel has to reach: four for 16x16
+    // tiles with uint8 or 3-product float32 operands (82 to 128 registers; uint16
+    // gets there by itself with 102 to 128), three for 6-product float32 (132 to
+    // 166), two for 32x32 tiles (116 to 176 registers: two to four waves).  None of
+    // them spills.
     static constexpr int WAVES =
         SHAPE == 16 ? (PM == kU8 || PM == kF32x3 ? 4 : 3) : 2;
-    // the persistent batched kernels need more registers: three waves for
-    // the 16-bit operand classes, the float32 classes as they come
+    // the persistent batched kernels need some 30 registers more: three waves for
+    // the 16-bit operand classes (134 to 158 on the default tile), the float32
+    // classes as they come (two or three waves); no spills there either
     static constexpr int BWAVES = SHAPE == 16 && (PM == kU8 || PM == kU16) ? 3 : 1;
 };
 

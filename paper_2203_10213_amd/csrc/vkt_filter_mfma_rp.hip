@@ -38,9 +38,9 @@
 // columns and 64 rows; a wave's 4 strips are adjacent, and one segment read
 // per (K chunk, operand piece) holds all their windows.
 //
-// What bounds it: the matrix cores (busy 77 % at 7^3, 57 % at 5^3 with 6
-// products, 37 % for uint8) at the clock that the card holds under them (1.5
-// to 1.7 GHz for float32).  Measured before and after the face quads of their
+// What bounds it: the matrix cores (busy 77 % at 7^3, 62 % at 5^3 with 6
+// products, 37 % for uint8) at the clock that the card holds under them (cycles
+// counted over the time: 1.3 GHz at 7^3, 1.9 at 5^3, 2.4 for uint8).  Measured before and after the face quads of their
 // own, the strips of three columns, the turning weights and the rising
 // priorities: 302^3 uint8 5^3 106 -> 46 us, 512^3 float32 5^3 with 6 products
 // 455 -> 409 us, 1024^3 7^3 with 3 products 2.97 -> 2.75 ms, all with the same

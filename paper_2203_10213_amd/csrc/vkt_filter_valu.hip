@@ -42,8 +42,8 @@ namespace {
 // the 512^3 5^3 workload; three spill SGPRs at k = 7.
 constexpr int kValuRowGroup = 2;
 // Waves per SIMD the single-volume kernel is compiled for: the 5^3 FP32
-// kernels fit 80 registers (six waves instead of five), measured 3.6 % faster
-// on the 512^3 workload; other sizes would spill a dozen registers and take
+// kernels fit 80 registers (six waves instead of five; float32 with one register
+// spilled, uint8 and uint16 with less), measured 3.6 % faster on the 512^3 workload; other sizes would spill a dozen registers and take
 // what they need.
 constexpr int valu_waves(int k, bool iacc) { return k == 5 && !iacc ? 6 : 1; }
 

@@ -164,8 +164,8 @@ __device__ inline void store16(void* p, uint4 v)
 // uint8 to 403^3: 401 us, 93 MB) were some 300 instructions a cell, most of
 // them the integer divisions of its three positions; here x and y positions
 // are worked out once per march and z positions once per workgroup (LDS), and
-// the same call takes 52 us at some 20 vector instructions a cell, which bound it
-// (the vector ALUs 66 % busy).
+// the same call takes 52 us at some 22 vector instructions a cell, which bound it
+// (the vector ALUs 63 % busy).
 constexpr int kZC = 32;   // destination planes per march at most
 constexpr int kXV = 4;    // adjacent destination cells per thread
 
