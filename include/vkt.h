@@ -206,9 +206,9 @@ vktError vktApplyFilterRange(vktStructuredVolume dst, vktStructuredVolume src,
  * sizes and filters of different k.  The pairs are grouped into arithmetic
  * classes (format, k, path); each class runs as one persistent launch whose
  * workgroups take tile-slabs of all its volumes from a work queue, longest
- * first; the class launches run side by side, on streams of the plan that fork
+ * first; the class launches run side by side, on streams of the library that fork
  * from the calling thread's stream and join it again.  The plan (descriptors,
- * work lists, weight pools, streams) is cached per batch signature -- volume
+ * work lists, weight pools) is cached per batch signature -- volume
  * pointers and dims, filter identities, mode, precision and stream; the 16 last
  * used are kept -- so a repeated batch is its launches alone.  While the stream
  * is being captured a batch whose plan is cached is recorded into the graph (and

@@ -13,8 +13,8 @@
 //     list is sorted longest first;
 //   * descriptors, work lists, the classes' weight pools and the work-queue
 //     counters go to one device buffer.
-// Launch: the class kernels side by side, on streams of the plan that fork from
-// the calling thread's stream and join it again.  Plans are cached by
+// Launch: the class kernels side by side, on streams that fork from the calling
+// thread's stream and join it again.  Plans are cached by
 // the batch's signature (pointers, dims, formats, filter identities, mode,
 // precision, stream), so a repeated batch is its launches alone.
 #include <algorithm>
@@ -149,39 +149,39 @@ struct ClassPlan {
     uint32_t nitems = 0;
 };
 
-// The streams on which a plan's classes run beside its caller's, with the
-// events that fork and join them.  A plan has a set of its own: shared by the
-// plans of two callers, a set would make one caller's kernels wait for the
-// other's stream.  Sets go back to a free list with their plan, so there are
-// no more than plans alive at once (the cache, the one that is made and the
-// captured ones), and are never destroyed.
+// The streams on which the classes of a batch run beside its caller's stream,
+// with the events that fork and join them.  The plans of one caller's stream share
+// a set, as their batches run one after another anyhow; shared by two callers, a set
+// would make one's kernels wait for the other's stream.  (With a set per plan more
+// streams share the hardware queues: 64 float32 volumes of 16 to 64 116 us, with this
+// 113; 2 of 17 to 40 79 and 77; larger batches the same.)  A set that the last of its plans has left is used for the next new stream, so there
+// are no more than streams with plans at once; none is ever destroyed.
 constexpr size_t kSideStreams = 3;  // (with the caller's, the 4 hardware queues)
 struct SideStreams {
     int device = 0;
+    hipStream_t caller = nullptr;
+    size_t plans = 0;  // that use it
     hipEvent_t fork = nullptr;
     hipStream_t stream[kSideStreams] = {};
     hipEvent_t joined[kSideStreams] = {};
     size_t n = 0;
 };
 std::mutex g_side_mu;
-std::vector<std::unique_ptr<SideStreams>> g_side_free;
+std::vector<std::unique_ptr<SideStreams>> g_side;
 
-// A set of n streams of the current device `dev`; null where they cannot be
-// made (the classes then run one after another).
-std::unique_ptr<SideStreams> take_side_streams(int dev, size_t n)
+// The set of the caller's stream on the current device `dev`, with at least n
+// streams; null where they cannot be made (the classes then run one after another).
+SideStreams* take_side_streams(int dev, hipStream_t caller, size_t n)
 {
-    std::unique_ptr<SideStreams> s;
-    {
-        std::lock_guard<std::mutex> lk(g_side_mu);
-        for (auto it = g_side_free.begin(); it != g_side_free.end(); ++it)
-            if ((*it)->device == dev) {
-                s = std::move(*it);
-                g_side_free.erase(it);
-                break;
-            }
-    }
+    std::lock_guard<std::mutex> lk(g_side_mu);
+    SideStreams* s = nullptr;
+    for (auto& x : g_side)
+        if (x->device == dev && x->plans && x->caller == caller) s = x.get();
+    for (auto& x : g_side)
+        if (!s && x->device == dev && !x->plans) s = x.get();
     if (!s) {
-        s = std::make_unique<SideStreams>();
+        g_side.push_back(std::make_unique<SideStreams>());
+        s = g_side.back().get();
         s->device = dev;
     }
     bool ok = s->fork || hipEventCreateWithFlags(&s->fork, hipEventDisableTiming) == hipSuccess;
@@ -192,10 +192,10 @@ std::unique_ptr<SideStreams> take_side_streams(int dev, size_t n)
              (ev || hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess);
         if (ok) ++s->n;
     }
-    if (ok) return s;
-    std::lock_guard<std::mutex> lk(g_side_mu);
-    g_side_free.push_back(std::move(s));
-    return nullptr;
+    if (!ok) return nullptr;
+    s->caller = caller;
+    ++s->plans;
+    return s;
 }
 
 struct Plan {
@@ -204,7 +204,7 @@ struct Plan {
     char* dbuf = nullptr;
     size_t dbytes = 0;
     std::vector<ClassPlan> classes;
-    std::unique_ptr<SideStreams> side;  // null: one class, or none to be had
+    SideStreams* side = nullptr;  // null: one class, or none to be had
     // recorded after every launch: an evicted plan is destroyed only once its
     // last launch has finished (it may still be queued on another thread's
     // stream when the plan leaves the cache)
@@ -219,7 +219,7 @@ struct Plan {
         if (dbuf) (void)hipFree(dbuf);
         if (side) {
             std::lock_guard<std::mutex> lk(g_side_mu);
-            g_side_free.push_back(std::move(side));
+            --side->plans;
         }
     }
 };
@@ -401,9 +401,9 @@ hipError_t launch_class(const ClassPlan& cp, hipStream_t s)
 // caller's stream).  Up to three leave the caller's lane empty, so that they start
 // together: the class there runs ahead of the others by the fork, and whichever it was
 // some batch became slower (256 uint8 volumes of 16 to 96, k = 3, 5, 7: with 3,
-// 5 or 7 there 258, 238 and 273 us, with none 243; 64 float32 of 16 to 64: 124,
-// 113 and 107, with none 115; 16 uint16 of 8 to 48: 86, 100 and 92, with none
-// 86).  One after another on the caller's stream the last three sets take 287,
+// 5 or 7 there 258, 238 and 273 us, with none 242; 64 float32 of 16 to 64: 124,
+// 113 and 107, with none 113; 16 uint16 of 8 to 48: 86, 100 and 92, with none
+// 84).  One after another on the caller's stream the last three sets take 287,
 // 141 and 115 us, as nodes of one graph they took 234, 114 and 88.
 hipError_t launch_plan(const Plan& p, hipStream_t s)
 {
@@ -600,7 +600,7 @@ vktError build_plan(const std::vector<Triple>& tr, std::vector<uintptr_t>&& sig,
     }
 
     if (plan->classes.size() > 1)
-        plan->side = take_side_streams(plan->device,
+        plan->side = take_side_streams(plan->device, stream,
                                        std::min(plan->classes.size(), kSideStreams));
     if (plan->side) assign_lanes(tr, *plan);
     e = hipEventCreateWithFlags(&plan->done, hipEventDisableTiming);
