@@ -534,7 +534,6 @@ vktError build_job(const vktStructuredVolume_* dst, const vktStructuredVolume_* 
         // weights add the 128 * sum(w) the cells lost by entering as s - 128
         const double D = (double)filt->divisor;
         j.r1 = allow_sep && filt->sep_ok ? &filt->r1 : nullptr;
-        j.r1_packs = !filt->q_signed && filt->sum_abs_int * 255 < (int64_t(1) << 16);
         j.q_bias = (float)(0.25 / D + (filt->q_signed ? 128.0 * (double)filt->sum_int / D : 0.0));
         // k = 3 with signed 8-bit weights: exact int8 products on the matrix
         // cores (cells always enter as s - 128) when the thread enables them

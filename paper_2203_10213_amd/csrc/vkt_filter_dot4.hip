@@ -133,27 +133,40 @@ __device__ inline void pin8(int32_t (&)[N][4])
     static_assert(N == 1 || N == 2, "rows per lane with scalar weight groups");
 }
 
-// Rank-1 filters w[c][b][a] = t[c] v[b] u[a] (exact integer factors): the dot
-// products run over one filter row, u, and the row sums are summed along y
-// with v and along z with t -- the dense sum, k + k multiply-adds and one row
-// of dot products instead of k^2 rows of them.  kPassPacked: two sums of 16
-// bits per register (unsigned weights with 255 sum(w) < 2^16), kPassInt: one.
-// (512^3 3^3 box: 71 us, dense 80; 400x380x360 5^3 box 56, dense 143; 7^3 box 88,
-// dense 296; with integer sums 3^3 would save nothing.)
-enum Passes { kDense = 0, kPassPacked = 1, kPassInt = 2 };
+// Rank-1 filters w[c][b][a] = t[c] v[b] u[a] (exact integer factors) in passes, all
+// sums in 32 bits: the dense sum.
+//  * Along x and y: for k = 3 dot products over the rows u v[b] of one filter plane;
+//    for k = 5, 7, and k = 3 with kPassesOnes, dot products over one row, u, and the
+//    row sums summed along y with v.
+//  * Along z: the ring holds the sums of the last k input planes, and an output is
+//    their sum weighted with t.
+// Tap weights of 1 are known at compile time for kPassesOnes (v and t all 1: box
+// filters) and, first and last, for kPassesUnit (binomial filters; the host factors v
+// and t without a common divisor): copies, additions and sums of three where the
+// others multiply.
+// us dense, with two sums of 16 bits a register (which unsigned filters of 255 sum(w)
+// below 2^16 had) and now, 512^3: 3^3 box 73, 55, 51, binomial 73, 55, 54, of other
+// factors 73, -, 58; 5^3 box 262, 83, 77; 7^3 box 510, -, 90; 400x380x360: 3^3 box 45,
+// 32, 30, 5^3 box 146, 55, 50, 7^3 box 305, -, 64.
+enum Passes { kDense = 0, kPasses = 1, kPassesUnit = 2, kPassesOnes = 3 };
 struct R1Args {
-    uint32_t u[2];           // packed 8-bit weights of a row
-    uint32_t v[7], t[7];     // kPassPacked: in both halves
+    uint32_t u[3][2];        // packed 8-bit weights of a row (r1_plane: of each row)
+    int32_t v[7], t[7];
 };
-typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-template <int MODE> struct Sum { typedef int32_t type; };
-template <> struct Sum<kPassPacked> { typedef u16x2 type; };
-__device__ inline u16x2 weight(uint32_t w, u16x2) { return __builtin_bit_cast(u16x2, w); }
-__device__ inline int32_t weight(uint32_t w, int32_t) { return (int32_t)w; }
-__device__ inline u16x2 wmul(u16x2 w, u16x2 x) { return w * x; }
-__device__ inline u16x2 wmac(u16x2 w, u16x2 x, u16x2 s) { return w * x + s; }
-__device__ inline int32_t wmul(int32_t w, int32_t x) { return __mul24(w, x); }
-__device__ inline int32_t wmac(int32_t w, int32_t x, int32_t s) { return __mul24(w, x) + s; }
+constexpr bool r1_plane(int k, int mode) { return k <= 3 && mode != kPassesOnes; }
+// w x + s, tap i of K (0: w x)
+template <int MODE, int K>
+__device__ inline int32_t tap(int i, int32_t w, int32_t x, int32_t s)
+{
+    if (MODE == kPassesOnes || (MODE == kPassesUnit && (i == 0 || i == K - 1)))
+        return i == 0 ? x : s + x;
+    if (i == 0) return __mul24(w, x);
+    // (unseen by the compiler, which would make two products and a sum of three of
+    // two multiply-adds)
+    int32_t r = __mul24(w, x) + s;
+    asm("" : "+v"(r));
+    return r;
+}
 
 // One tile-slab: output tile `tile` of z-slab `slab` of volume a.
 template <int K, bool SG, int VYO = 0, int MODE = kDense>
@@ -161,8 +174,6 @@ __device__ void dot4_tile(const VolDesc& a, const uint32_t* __restrict__ wq, int
                           int slab, uint32_t* lds, const R1Args& r1 = R1Args{})
 {
     using G = Geo4<K, VYO>;
-    using S = typename Sum<MODE>::type;
-    constexpr int NS = MODE == kPassPacked ? 2 : 4;  // registers of 4 sums
     constexpr int R = G::R, VY = G::VY, NH = G::NH;
     const uint8_t* __restrict__ src = static_cast<const uint8_t*>(a.src);
     uint8_t* __restrict__ dst = static_cast<uint8_t*>(a.dst);
@@ -256,13 +267,13 @@ __device__ void dot4_tile(const VolDesc& a, const uint32_t* __restrict__ wq, int
             face ? fbyte[0] | fbyte[1] << 8 | fbyte[2] << 16 | fbyte[3] << 24 : stage[NI];
     };
 
-    S acc[K][VY][NS];
+    int32_t acc[K][VY][4];
 #pragma unroll
     for (int c = 0; c < K; ++c)
 #pragma unroll
         for (int vy = 0; vy < VY; ++vy)
 #pragma unroll
-            for (int j = 0; j < NS; ++j) acc[c][vy][j] = S(0);
+            for (int j = 0; j < 4; ++j) acc[c][vy][j] = 0;
 
     const int zi_beg = zb - R;
     const int nz = ze - zb;           // output planes of the slab
@@ -291,7 +302,8 @@ __device__ void dot4_tile(const VolDesc& a, const uint32_t* __restrict__ wq, int
         const uint32_t* buf = lds + (p & 1) * G::PLANE_BUF + (wave * VY) * G::WD + lane;
 
         if constexpr (MODE != kDense) {
-            S pv[VY][NS];  // this plane's sums over x and y
+            constexpr bool PLANE = r1_plane(K, MODE);
+            int32_t (&pv)[VY][4] = acc[U];  // sums over x and y
 #pragma unroll
             for (int jr = 0; jr < G::NROW; ++jr) {
                 uint32_t L = buf[jr * G::WD], C = buf[jr * G::WD + 1], Rr = buf[jr * G::WD + 2];
@@ -301,43 +313,25 @@ __device__ void dot4_tile(const VolDesc& a, const uint32_t* __restrict__ wq, int
                     Rr ^= 0x80808080u;
                 }
                 int32_t d[4] = {0, 0, 0, 0};
+                uint32_t win[4];
                 static_for<4 * NH>([&](auto qc) {
                     constexpr int h = decltype(qc)::value / 4, j = decltype(qc)::value % 4;
-                    d[j] = dot4<SG>(window<j - R + 4 * h>(L, C, Rr), r1.u[h], d[j]);
+                    win[j] = window<j - R + 4 * h>(L, C, Rr);
+                    if constexpr (!PLANE) d[j] = dot4<SG>(win[j], r1.u[0][h], d[j]);
                 });
-                S x[NS];
-                if constexpr (MODE == kPassPacked) {
-#pragma unroll
-                    for (int j = 0; j < 2; ++j)
-                        x[j] = __builtin_bit_cast(
-                            u16x2, (uint32_t)d[2 * j] | (uint32_t)d[2 * j + 1] << 16);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) x[j] = d[j];
-                }
 #pragma unroll
                 for (int vy = 0; vy < VY; ++vy) {
                     const int b = jr - vy;
                     if (b < 0 || b >= K) continue;
 #pragma unroll
-                    for (int j = 0; j < NS; ++j)
-                        pv[vy][j] = b == 0 ? wmul(weight(r1.v[0], S{}), x[j])
-                                           : wmac(weight(r1.v[b], S{}), x[j], pv[vy][j]);
+                    for (int j = 0; j < 4; ++j) {
+                        if constexpr (PLANE)
+                            pv[vy][j] = dot4<SG>(win[j], r1.u[b][0], b == 0 ? 0 : pv[vy][j]);
+                        else
+                            pv[vy][j] = tap<MODE, K>(b, r1.v[b], d[j], pv[vy][j]);
+                    }
                 }
             }
-            static_for<K>([&](auto cc) {
-                constexpr int c = decltype(cc)::value;
-                constexpr int slot = ((U - c) % K + K) % K;
-                // (planes outside the slab are never stored)
-                if (p - c < 0 || p - c >= nz) return;
-#pragma unroll
-                for (int vy = 0; vy < VY; ++vy)
-#pragma unroll
-                    for (int j = 0; j < NS; ++j)
-                        acc[slot][vy][j] = c == 0 ? wmul(weight(r1.t[0], S{}), pv[vy][j])
-                                                  : wmac(weight(r1.t[c], S{}), pv[vy][j],
-                                                         acc[slot][vy][j]);
-            });
         } else if constexpr (K <= 3) {
             // stream the input rows: the 4 windows of row jr feed every
             // (output row vy, filter row b = jr - vy, filter plane c)
@@ -424,10 +418,15 @@ __device__ void dot4_tile(const VolDesc& a, const uint32_t* __restrict__ wq, int
                 uint32_t packed = 0;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    float sum;
-                    if constexpr (MODE == kPassPacked) sum = (float)acc[done][vy][j / 2][j % 2];
-                    else sum = (float)acc[done][vy][j];
-                    packed = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(sum, inv_D, bias), j, packed);
+                    int32_t sum = acc[done][vy][j];
+                    if constexpr (MODE != kDense) {
+                        // slot `done` holds the first of the k planes' sums
+                        sum = tap<MODE, K>(0, r1.t[0], sum, 0);
+#pragma unroll
+                        for (int c = 1; c < K; ++c)
+                            sum = tap<MODE, K>(c, r1.t[c], acc[(done + c) % K][vy][j], sum);
+                    }
+                    packed = __builtin_amdgcn_cvt_pk_u8_f32(fmaf((float)sum, inv_D, bias), j, packed);
                 }
                 *reinterpret_cast<uint32_t*>(dst + zo * plane + (int64_t)y * a.X + ox) = packed;
             }
@@ -492,15 +491,17 @@ void filter_dot4_batched_kernel(BatchArgs b)
     }
 }
 
-// Output rows per lane of the rank-1 kernels (3^3 with 8 rows: 75 us on 512^3,
-// 18.0 on 256^3; with 4 rows 71 and 12.9).
+// Output rows per lane of the rank-1 kernels: with 3 or 2 the rows above and below
+// are read and multiplied for fewer outputs (512^3 5^3 box 88 -> 107 us, before the
+// ring of plane sums), with 6 they spill.
 constexpr int kR1Rows = 4;
-// Waves per SIMD: four where the sums fit 128 registers (3^3 71, packed 5^3 96 and
-// 7^3 117); sums of 32 bits take 153 and 189 for 5^3 and 7^3 and would spill.
-constexpr int r1_waves(int k, int mode) { return k <= 3 || mode == kPassPacked ? 4 : 2; }
+// Waves per SIMD: what they get without spills (k = 3: 86 to 95 registers, 5: 127 to
+// 131, 7: 163 to 166); held to one more 512^3 3^3 box 52 -> 115 us and 5^3 of other
+// factors 119 -> 128.
+constexpr int r1_waves(int k) { return k <= 3 ? 5 : k <= 5 ? 3 : 2; }
 
 template <int K, bool SG, int MODE>
-__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(r1_waves(K, MODE))))
+__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(r1_waves(K))))
 void filter_dot4_r1_kernel(VolDesc a, R1Args r1, uint32_t nblocks)
 {
     constexpr int VY = kR1Rows;
@@ -523,25 +524,29 @@ hipError_t launch_r1(const FilterJob& j, hipStream_t s)
     if (nb > 0x7fffffff) return hipErrorInvalidValue;
     R1Args r{};
     for (int i = 0; i < K; ++i) {
-        const uint32_t both = MODE == kPassPacked ? 0x10001u : 1u;
-        r.u[i / 4] |= ((uint32_t)j.r1->u[i] & 0xffu) << (8 * (i % 4));
-        r.v[i] = (uint32_t)j.r1->v[i] * both;
-        r.t[i] = (uint32_t)j.r1->t[i] * both;
+        // (u[i] v[b] is a weight over t's, of at least 1 in magnitude: 8 bits as well)
+        for (int b = 0; b < (r1_plane(K, MODE) ? K : 1); ++b)
+            r.u[b][i / 4] |= ((uint32_t)(j.r1->u[i] * (r1_plane(K, MODE) ? j.r1->v[b] : 1)) & 0xffu)
+                             << (8 * (i % 4));
+        r.v[i] = j.r1->v[i];
+        r.t[i] = j.r1->t[i];
     }
     hipLaunchKernelGGL((filter_dot4_r1_kernel<K, SG, MODE>), dim3((unsigned)nb), dim3(kNT), 0, s, a,
                        r, (uint32_t)nb);
     return hipGetLastError();
 }
 
-// Dense or, for rank-1 filters (3^3 only where the sums pack), in passes.
+// Dense or, for rank-1 filters, in passes.
 template <int K, bool SG>
 hipError_t launch_k(const FilterJob& j, hipStream_t s)
 {
-    if constexpr (!SG) {
-        if (j.r1 && j.r1_packs) return launch_r1<K, SG, kPassPacked>(j, s);
-    }
-    if constexpr (K > 3) {
-        if (j.r1) return launch_r1<K, SG, kPassInt>(j, s);
+    if (j.r1) {
+        const Rank1Int& f = *j.r1;
+        bool unit = f.t[0] == 1 && f.t[K - 1] == 1, ones = true;
+        if (K > 3) unit = unit && f.v[0] == 1 && f.v[K - 1] == 1;
+        for (int i = 0; i < K; ++i) ones = ones && f.v[i] == 1 && f.t[i] == 1;
+        if (ones) return launch_r1<K, SG, kPassesOnes>(j, s);
+        return unit ? launch_r1<K, SG, kPassesUnit>(j, s) : launch_r1<K, SG, kPasses>(j, s);
     }
     const ClassGeom g = dot4_geom(K);
     // the output region's tiles and z extent (the whole volume unless a range)

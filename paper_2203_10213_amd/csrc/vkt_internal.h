@@ -103,7 +103,6 @@ struct FilterJob {
     const uint32_t* wq;      // device packed weights
     float q_bias;            // epilogue constant of the dot-product path
     const Rank1Int* r1;      // factors of a rank-1 filter on it (host), or null
-    bool r1_packs;           // its sums fit 16 bits, unsigned
     bool i8mma;              // uint8 cells, k = 3, int8 matrix-core path
     const uint32_t* wm;      // device W operands of that path
     float m8_bias;           // its epilogue constant: (1/4 + 128 sum(w)) / D
