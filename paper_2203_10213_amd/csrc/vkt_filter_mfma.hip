@@ -256,12 +256,12 @@ __device__ void mfma_tile(const VolDesc& a, const float* __restrict__ w, int til
     constexpr int BY = C::BY, CPL = C::CPL;
     float* const blk = epi + wave * C::WX * BY;
     const int lrow = lane % BY, lpart = lane / BY;
-    const int xt = C::WX * wave + CPL * lpart, yl = y0 + lrow;
-    const int nx = a.rx1 - x0 - xt;  // cells left in the row
+    // (columns past 2^31 - 1 wrap to negative ones, whose offsets lie past the plane)
+    const int xw = (int)((uint32_t)x0 + (uint32_t)(C::WX * wave + CPL * lpart)), yl = y0 + lrow;
     // rows past the volume's last row fall beyond the plane: dropped
     const uint32_t ooff =
-        yl < a.ry1 ? ((uint32_t)yl * (uint32_t)a.X + (uint32_t)x0 + (uint32_t)xt) * (uint32_t)sizeof(T) : kOutside;
-    const bool vec_row = nx >= CPL;  // (buffer stores take any cell alignment)
+        yl < a.ry1 ? ((uint32_t)yl * (uint32_t)a.X + (uint32_t)xw) * (uint32_t)sizeof(T) : kOutside;
+    const bool vec_row = xw <= a.rx1 - CPL;  // (buffer stores take any cell alignment)
 
     acc_t acc[C::MTW];
 #pragma unroll
@@ -388,7 +388,7 @@ __device__ void mfma_tile(const VolDesc& a, const float* __restrict__ w, int til
             const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
                 static_cast<char*>(a.dst) + (int64_t)zo * plane_bytes, (short)0, plane_bytes,
                 (int)kRsrcWord3);
-            store_row<T, CPL>(rd, ooff, v, vec_row, nx, a.unscale);
+            store_row<T, CPL>(rd, ooff, v, vec_row, a.rx1 - xw, a.unscale);
             asm volatile("" ::: "memory");
         }
         // ---- advance the ring

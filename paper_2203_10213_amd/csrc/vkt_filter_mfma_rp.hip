@@ -196,12 +196,12 @@ __device__ void rp_tile(const VolDesc& a, const float* __restrict__ w, int tile,
     constexpr int CP = C::TX / 4;
     typedef float evec __attribute__((ext_vector_type(C::EV)));
     const int srow = t / 4, scol = CP * (t % 4);
-    const int ys = y0 + srow, nx = a.rx1 - x0 - scol;  // nx: cells left in the row
+    // (columns past 2^31 - 1 wrap to negative ones, whose offsets lie past the plane)
+    const int ys = y0 + srow, xst = (int)((uint32_t)x0 + (uint32_t)scol);
     // rows past the region's last row fall beyond the plane: dropped
     const uint32_t ooff =
-        ys < a.ry1 ? ((uint32_t)ys * (uint32_t)a.X + (uint32_t)x0 + (uint32_t)scol) * (uint32_t)sizeof(T)
-                   : kOutside;
-    const bool vec_row = nx >= CP;  // (buffer stores take any cell alignment)
+        ys < a.ry1 ? ((uint32_t)ys * (uint32_t)a.X + (uint32_t)xst) * (uint32_t)sizeof(T) : kOutside;
+    const bool vec_row = xst <= a.rx1 - CP;  // (buffer stores take any cell alignment)
 
     f32x16 acc[C::WS];
 #pragma unroll
@@ -331,7 +331,7 @@ __device__ void rp_tile(const VolDesc& a, const float* __restrict__ w, int tile,
             const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
                 static_cast<char*>(a.dst) + (int64_t)zo * plane_bytes, (short)0, plane_bytes,
                 (int)kRsrcWord3);
-            store_row<T, CP>(rd, ooff, v, vec_row, nx, a.unscale);
+            store_row<T, CP>(rd, ooff, v, vec_row, a.rx1 - xst, a.unscale);
         }
         cur ^= 1;
     };

@@ -181,14 +181,14 @@ __device__ __attribute__((always_inline)) inline void sep_tile(
     if (zi_beg + 1 < zi_end) in.gather(a, zi_beg + 1);
     __syncthreads();
 
-    const int nx = a.rx1 - x0 - kVX * tx, oy = y0 + kVY * ty;  // nx: cells left in the row
-    const uint32_t ox = (uint32_t)x0 + (uint32_t)(kVX * tx);
-    const bool vec = nx >= kVX;
+    // (columns past 2^31 - 1 wrap to negative ones, whose offsets lie past the plane)
+    const int ox = (int)((uint32_t)x0 + (uint32_t)(kVX * tx)), oy = y0 + kVY * ty;
+    const bool vec = ox <= a.rx1 - kVX;
     uint32_t ooff[kVY];  // this thread's output rows (past the region: dropped)
 #pragma unroll
     for (int vy = 0; vy < kVY; ++vy)
         ooff[vy] = oy + vy < a.ry1
-                       ? ((uint32_t)(oy + vy) * (uint32_t)a.X + ox) * (uint32_t)sizeof(T)
+                       ? ((uint32_t)(oy + vy) * (uint32_t)a.X + (uint32_t)ox) * (uint32_t)sizeof(T)
                        : kOutside;
 
     auto step = [&](int zi, auto U) __attribute__((always_inline)) {
@@ -274,7 +274,7 @@ __device__ __attribute__((always_inline)) inline void sep_tile(
                 T r4[kVX];
 #pragma unroll
                 for (int vx = 0; vx < kVX; ++vx) r4[vx] = finish<T>(acc[old][vy][vx], a);
-                store4<T>(d, ooff[vy], r4, vec, nx);
+                store4<T>(d, ooff[vy], r4, vec, a.rx1 - ox);
             }
         }
     };

@@ -132,7 +132,7 @@ struct PlaneStage {
         const int32_t plane_cells = a.X * a.Y;
         // staged columns up to the volume's right face, at most one quad past the
         // tile (X may be as large as 2^31 - 1: no sum of it and a width)
-        const int cols = (int)min((int64_t)a.X - xl, (int64_t)COLS + 4);
+        const int cols = (int)min((uint32_t)a.X - (uint32_t)xl, (uint32_t)(COLS + 4));
         face = xl < 0 || cols < COLS;
         inner = 0;
         if constexpr (LINEAR) {
@@ -147,10 +147,14 @@ struct PlaneStage {
             const int gy = addr_map((int64_t)y0 - R + hy, a.Y, a.mode);
             // (a face quad's load stays inside the plane; it is not staged; a
             // row outside the volume under border mode reads 0; in planes of
-            // fewer than 4 cells every quad is a face quad)
-            const int32_t cell = min(max(gy, 0) * a.X + max(xl + min(hx, cols - 1), 0), plane_cells - 4);
+            // fewer than 4 cells every quad is a face quad; columns past 2^31 - 1
+            // wrap to negative ones: face quads as well)
+            const int xs = (int)((uint32_t)xl + (uint32_t)hx);
+            const int32_t cell = min((int32_t)((uint32_t)max(gy, 0) * (uint32_t)a.X +
+                                               (uint32_t)max(xs, 0)),
+                                     plane_cells - 4);
             goff[i] = gy < 0 || cell < 0 ? kOutside : (uint32_t)cell * (uint32_t)sizeof(T);
-            if (hx >= -xl && hx + 3 < cols) inner |= 1u << i;
+            if (xs >= 0 && xs < a.X - 3) inner |= 1u << i;
         }
 #pragma unroll
         for (int i = 0; i < NF; ++i) fpos[i] = -1;
