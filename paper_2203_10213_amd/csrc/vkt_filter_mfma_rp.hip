@@ -38,7 +38,7 @@
 // columns and 64 rows; a wave's 4 strips are adjacent, and one segment read
 // per (K chunk, operand piece) holds all their windows.
 //
-// What bounds it: the matrix cores (busy 77 % at 7^3, 62 % at 5^3 with 6
+// What bounds it: the matrix cores (busy 78 % at 7^3, 60 % at 5^3 with 6
 // products, 37 % for uint8) at the clock that the card holds under them (cycles
 // counted over the time: 1.3 GHz at 7^3, 1.9 at 5^3, 2.4 for uint8).  Measured before and after the face quads of their
 // own, the strips of three columns, the turning weights and the rising
